@@ -245,15 +245,12 @@ def main():
     prof_updates = float(H * W * C * n_prof)
     nl = max(int(launches[1]), 1)
     pass_ms = kms[1] / nl
-    terms, evals, direct, anchors, aterms, fused = [float(x) for x in work]
+    terms, evals, direct, anchors, aterms = [float(x) for x in work[:5]]
     series = sched_used in (bdc.BDC_SCHED_BLOCK_SERIES, bdc.BDC_SCHED_BLOCK9_SERIES)
     if series:
-        # executed algorithmic work: series evaluations, direct evaluations' phi
-        # terms (5 operations each; those of an accepted move's PSF-core entries,
-        # a share fused / direct of them, also build the series at the new mean:
-        # 12 more) and the anchors' phi terms
-        ops = (OPS_PER_SERIES_EVAL * (evals - direct) + OPS_PER_TERM * terms
-               + OPS_PER_ANCHOR_TERM * terms * (fused / max(direct, 1.0)) + OPS_PER_ANCHOR_TERM * aterms)
+        # executed algorithmic work: series evaluations, the phi terms of the
+        # few direct evaluations (5 operations each) and those of the anchors
+        ops = OPS_PER_SERIES_EVAL * (evals - direct) + OPS_PER_TERM * terms + OPS_PER_ANCHOR_TERM * aterms
         kbar = aterms / max(anchors, 1.0)      # window length at the current state
     else:
         ops = OPS_PER_TERM * terms
@@ -274,7 +271,7 @@ def main():
             "footprint_evals_per_update": evals / prof_updates,
             "slots_per_update": alg_ops / prof_updates,
             "direct_evals_per_update": direct / prof_updates if series else evals / prof_updates,
-            "anchors_per_update": (anchors + fused) / prof_updates,
+            "anchors_per_update": anchors / prof_updates,
             "executed": {"ops_per_update": ops / prof_updates, "achieved": executed / 1e12,
                          "frac": executed / PEAK_VALU_OPS},
             "hbm_alg_frac": (BYTES_PER_UPDATE * updates / (ms / 1e3)) / PEAK_HBM,

@@ -133,6 +133,19 @@ __device__ inline void recip4(int n, double cv[4]) {
     cv[3] = nc * Rab;
 }
 
+// 1/x: the hardware reciprocal (about 27 bits) and one Newton step; rcp_nr2: two
+// steps, full double accuracy.
+__device__ inline double rcp_nr(double x) {
+    const double r = __builtin_amdgcn_rcp(x);
+    return r * fma(-x, r, 2.0);
+}
+
+__device__ inline double rcp_nr2(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return fma(r, fma(-x, r, 1.0), r);
+}
+
 // ---------------------------------------------------------------------------
 // phi window.  For mean mu the log-summand f(k) = -a (k-c)^2 + k log mu - lgamma(k+1)
 // is concave with f'' <= -(2a + 1/(k+1)).  Its continuous mode k* lies where
@@ -252,18 +265,21 @@ __device__ __noinline__ double delta_ell_sharp(float d, float lmu, float lx, Win
 //   ell(mu + y) - ell(mu) = b1 y + b2 y^2 + b3 y^3 + b4 y^4,
 //   b1 = h1/mu - 1, bj = hj/mu^j,
 // and the radius R = u mu, the largest |y| whose bound stays below
-// SERIES_TAU / 2 (u <= 1/2, so mu + y > 0 inside it).  R = 0 (always
-// evaluate directly) for sharp read noise, an unusable window or mu <= 0.
+// SERIES_TAU / 2 (u <= 1/2, so mu + y > 0 inside it).  R = 0 (never used in
+// place of the direct evaluation) for sharp read noise, whose coefficients serve
+// the bounds of series_bound only, and, with b2 > 0 (no
+// series has it), for an unusable window or mu <= 0.
 // ---------------------------------------------------------------------------
 constexpr float SERIES_TAU = 3e-9f;
 
 struct Series { float4 b; float R; };
+__device__ inline float4 no_series() { return make_float4(0.0f, 1.0f, 0.0f, 0.0f); }
 
-// Series of the pixel at mean mu from the window polynomial
-// A(v) = sum_{k > lo} (W_k / W_lo)(1 + v)^(k - lo) (coefficients A0..A4).
-__device__ inline Series series_finish(double A0, double A1, double A2, double A3, double A4, int lo, float mu) {
+// Series of the pixel at mean mu from the window polynomial S(v) =
+// sum_k (W_k / W_ref)(1 + v)^(k - lo) (coefficients S0, A1..A4).
+__device__ inline Series series_finish(double S0, double A1, double A2, double A3, double A4, int lo, float mu) {
     Series out;
-    const double iS = 1.0 / (1.0 + A0);
+    const double iS = rcp_nr2(S0);
     const double s1 = A1 * iS, s2 = A2 * iS, s3 = A3 * iS, s4 = A4 * iS;
     // log(1 + s1 v + s2 v^2 + ...): h_j = s_j - (1/j) sum_{i<j} i h_i s_{j-i}
     const double h1 = s1;
@@ -272,7 +288,7 @@ __device__ inline Series series_finish(double A0, double A1, double A2, double A
     const double h4 = s4 - 0.25 * (h1 * s3 + 2.0 * h2 * s2 + 3.0 * h3 * s1);
     const double L = (double)lo;                     // + lo log(1 + v)
     const double g1 = h1 + L, g2 = h2 - 0.5 * L, g3 = h3 + L * (1.0 / 3.0), g4 = h4 - 0.25 * L;
-    const double im = 1.0 / (double)mu, im2 = im * im;
+    const double im = rcp_nr2((double)mu), im2 = im * im;
     out.b = make_float4((float)(g1 * im - 1.0), (float)(g2 * im2), (float)(g3 * im2 * im), (float)(g4 * im2 * im2));
     // radius: u0 = (tau/2 * 5 / s2)^(1/5) solves s2 u^5 / 5 = tau/2; the factor
     // (1 - u0)^(1/5) makes room for the 1/(1 - u) of the bound
@@ -281,6 +297,41 @@ __device__ inline Series series_finish(double A0, double A1, double A2, double A
     u = fminf(u, 0.5f);
     u *= __builtin_amdgcn_exp2f(0.2f * __builtin_amdgcn_logf(1.0f - u));
     out.R = u * mu;
+    return out;
+}
+
+// Sharp read noise (a > A_RECUR_MAX): the few weights of the window relative to
+// the one nearest to c, outwards by their ratios; R = 0.
+__device__ __noinline__ Series series_sharp(float mu, Window win, float c, float a2) {
+    int k0 = (int)rintf(fmaxf(c, 0.0f));
+    k0 = k0 < win.lo ? win.lo : (k0 > win.hi ? win.hi : k0);
+    double S0 = 0.0, S1 = 0.0, S2 = 0.0, S3 = 0.0, S4 = 0.0;
+    auto add = [&](int k, double w) {
+        const double n = (double)(k - win.lo);
+        S0 += w;
+        w *= n;
+        S1 += w;
+        w *= (n - 1.0) * 0.5;
+        S2 += w;
+        w *= (n - 2.0) * (1.0 / 3.0);
+        S3 += w;
+        S4 += w * (n - 3.0) * 0.25;
+    };
+    auto ratio = [&](int k) { return (double)mu * exp_wide(-(double)a2 * ((double)k + 0.5 - (double)c)); };   // (k + 1) W_(k+1) / W_k
+    double w = 1.0;
+    add(k0, w);
+    for (int k = k0; k < win.hi && w > 1e-30; ++k) {
+        w *= ratio(k) * rcp_nr((double)(k + 1));
+        add(k + 1, w);
+    }
+    w = 1.0;
+    for (int k = k0 - 1; k >= win.lo && w > 1e-30; --k) {
+        w *= (double)(k + 1) * exp_wide((double)a2 * ((double)k + 0.5 - (double)c)) * rcp_nr((double)mu);
+        add(k, w);
+    }
+    Series out = series_finish(S0, S1, S2, S3, S4, win.lo, mu);
+    out.R = 0.0f;
+    if (!(fabsf(out.b.x) + fabsf(out.b.y) + fabsf(out.b.z) + fabsf(out.b.w) < INFINITY)) out.b = no_series();
     return out;
 }
 
@@ -305,11 +356,6 @@ __device__ inline Series series_finish(double A0, double A1, double A2, double A
 // products (hardware reciprocal and one Newton step, full double accuracy),
 // so the chain is multiplies and adds only; the tolerance is checked once per
 // step (the extra terms of the last step only add more of the exact sum).
-__device__ inline double rcp_nr(double x) {
-    const double r = __builtin_amdgcn_rcp(x);
-    return r * fma(-x, r, 2.0);
-}
-
 __device__ inline double log_i1(double z) {
     if (z < 24.0) {
         const double h = 0.5 * z, h2 = h * h;
@@ -383,19 +429,11 @@ __device__ inline double delta_ell_emccd(float mu, float d, const PixConst& pc) 
 // normalisation at lo cannot overflow.  Returns NaN when mu + d <= 0 or on
 // overflow (the caller then rejects).  inv_tab[k] = 1/k for k < INV_TABLE.
 // ---------------------------------------------------------------------------
-// With ANCHOR, the same window also yields the local series at mu + d (the
-// tilted weights W_k x^k are the posterior weights there), for the caller to
-// install if the move is accepted; next->R = 0 where no series is formed.
 // TABLE: 1/(k+1) from inv_tab (staged in LDS by the caller), else computed
 // (recip4), which keeps memory latency out of the recurrence when no table
 // fits in LDS.
-template <bool ANCHOR, bool TABLE = true>
-__device__ inline double delta_ell_t(float mu, float d, const PixConst& pc, const double* inv_tab, int& nterms,
-                                     Series* next) {
-    if (ANCHOR) {
-        next->R = 0.0f;
-        next->b = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    }
+template <bool TABLE>
+__device__ inline double delta_ell_t(float mu, float d, const PixConst& pc, const double* inv_tab, int& nterms) {
     const float mu1 = mu + d;
     if (!(mu1 > 0.0f) || !(mu > 0.0f)) return __builtin_nan("");
     if (d == 0.0f) return 0.0;
@@ -419,7 +457,6 @@ __device__ inline double delta_ell_t(float mu, float d, const PixConst& pc, cons
     // |exponent| <= 2 A_RECUR_MAX (2^20 + 1): within exp_wide_b's range
     double G = (double)mu * exp_wide_b(-(double)pc.a2 * ((double)k_top + 0.5 - (double)pc.c));
     double acc0 = 0.0, acc1 = 0.0;
-    double A0 = 0.0, A1 = 0.0, A2 = 0.0, A3 = 0.0, A4 = 0.0;   // series polynomial at mu + d
     if (!TABLE || hi < INV_TABLE) {
         const double* iv = inv_tab + hi;          // iv[-i] = 1 / (hi - i)
 #pragma unroll 1
@@ -438,14 +475,6 @@ __device__ inline double delta_ell_t(float mu, float d, const PixConst& pc, cons
                 acc0 = fma(r, acc0, r);
                 const double rx = r * x;
                 acc1 = fma(rx, acc1, rx);
-                if (ANCHOR) {
-                    const double T0 = A0 + 1.0;
-                    A4 = rx * (A4 + A3);
-                    A3 = rx * (A3 + A2);
-                    A2 = rx * (A2 + A1);
-                    A1 = rx * (A1 + T0);
-                    A0 = rx * T0;
-                }
             }
         }
     } else {
@@ -456,126 +485,239 @@ __device__ inline double delta_ell_t(float mu, float d, const PixConst& pc, cons
             acc0 = fma(r, acc0, r);
             const double rx = r * x;
             acc1 = fma(rx, acc1, rx);
-            if (ANCHOR) {
-                const double T0 = A0 + 1.0;
-                A4 = rx * (A4 + A3);
-                A3 = rx * (A3 + A2);
-                A2 = rx * (A2 + A1);
-                A1 = rx * (A1 + T0);
-                A0 = rx * T0;
-            }
         }
     }
-    if (ANCHOR) *next = series_finish(A0, A1, A2, A3, A4, lo, mu + d);
     // log((1 + acc1)/(1 + acc0)): the sums are normalised at the window's low
     // end and may exceed the FP32 range, so the ratio stays in double.
     return fma((double)lo, (double)lx, log_ratio(1.0 + acc1, 1.0 + acc0) - (double)d);
 }
 
 __device__ inline double delta_ell(float mu, float d, const PixConst& pc, const double* inv_tab, int& nterms) {
-    return delta_ell_t<false>(mu, d, pc, inv_tab, nterms, nullptr);
+    return delta_ell_t<true>(mu, d, pc, inv_tab, nterms);
 }
 
 // The same without a reciprocal table.
 __device__ inline double delta_ell_notab(float mu, float d, const PixConst& pc, int& nterms) {
-    return delta_ell_t<false, false>(mu, d, pc, nullptr, nterms, nullptr);
+    return delta_ell_t<false>(mu, d, pc, nullptr, nterms);
 }
 
-// A direct evaluation whose series at mu + d is formed only once the move is
-// accepted.  delta_ell_keep returns what delta_ell_t<false, false> returns and
-// keeps what the window's recurrence needs beyond (mu, d); series_kept(k, mu,
-// d) then recomputes x = 1 + d / mu and exp(2a) by the same operations, runs
-// the same terms (the products of the ANCHOR pass, in its order, so the series
-// is bit-identical to that pass's) and returns the series at mu + d, with
-// R = 0 where the evaluation forms none (no move, a rejected window, sharp read
-// noise).  A rejected move, about half of them, skips the series' work: the
-// polynomial recurrence is two thirds of each term's operations.  The kept
-// state is five registers, as many as the series it replaces.
-struct DirectKeep {
-    double G;    // G at the window top
-    int hi, n4;  // window [hi - n4, hi), widened to a multiple of four terms; n4 < 0: no series
-    float a2;    // 2a of the pixel
+// Change of the series between displacements y0 = D and y1 = D + d from the
+// anchor, as d times the divided difference of the polynomial (Horner on both
+// points at once), so it stays proportional to d without cancellation.
+__device__ inline float series_delta(float4 b, float D, float d) {
+    const float y1 = D + d;
+    float q = b.w;
+    float p = fmaf(b.w, D, b.z);
+    q = fmaf(q, y1, p);
+    p = fmaf(p, D, b.y);
+    q = fmaf(q, y1, p);
+    p = fmaf(p, D, b.x);
+    q = fmaf(q, y1, p);
+    return d * q;
+}
+
+// The direct evaluation of the block-series scans, and the series an accepted
+// move's pixel takes when it leaves its radius.  Both run over one window, that
+// of [mu, mu + d], set up by direct_window: delta_ell_direct sums the two
+// Horner recurrences over it, series_after forms the series at mu + d from it
+// (the tilted weights W_k x^k are the posterior weights there).
+struct DirectWindow {
+    double x, qi, G;   // 1 + d / mu, exp(2a), G at the window top
+    float lx;          // log x
+    int lo, hi, n;     // window [lo, hi), widened to a multiple of four terms
+    int terms;         // the window's terms (work measure)
+    int kind;          // 0: the recurrence, 1: no value (the caller rejects), 2: sharp read noise
+    Window win;        // the window before widening (kind 2)
+    float lmu;
 };
 
-__device__ inline double delta_ell_keep(float mu, float d, const PixConst& pc, int& nterms, DirectKeep& k) {
-    k.n4 = -1;
+__device__ inline DirectWindow direct_window(float mu, float d, const PixConst& pc) {
+    DirectWindow w;
+    w.terms = 0;
+    w.kind = 1;
     const float mu1 = mu + d;
-    if (!(mu1 > 0.0f) || !(mu > 0.0f)) return __builtin_nan("");
-    if (d == 0.0f) return 0.0;
+    if (!(mu1 > 0.0f) || !(mu > 0.0f)) return w;
     const float t = d * fast_rcp(mu);
-    const float lx = log1p_k(t);
-    const float lmu = fast_ln(mu);
-    const Window win = phi_window(lmu + fminf(lx, 0.0f), lmu + fmaxf(lx, 0.0f), pc);
-    if (!win.ok) return __builtin_nan("");
-    nterms += win.hi - win.lo + 1;
-    if (pc.a2 > 2.0f * A_RECUR_MAX) return delta_ell_sharp(d, lmu, lx, win, pc);
-    int lo = win.lo, hi = win.hi;
-    const int n4 = (hi - lo + 3) & ~3;
-    lo = hi - n4;
-    if (lo < 0) { hi -= lo; lo = 0; }
-    const double x = 1.0 + (double)t;
-    const double qi = exp_small(pc.a2);
-    double G = (double)mu * exp_wide_b(-(double)pc.a2 * ((double)(hi - 1) + 0.5 - (double)pc.c));
-    k.G = G;
-    k.hi = hi;
-    k.n4 = n4;
-    k.a2 = pc.a2;
+    w.lx = log1p_k(t);
+    w.lmu = fast_ln(mu);
+    w.win = phi_window(w.lmu + fminf(w.lx, 0.0f), w.lmu + fmaxf(w.lx, 0.0f), pc);
+    if (!w.win.ok) return w;
+    w.terms = w.win.hi - w.win.lo + 1;
+    if (pc.a2 > 2.0f * A_RECUR_MAX) {
+        w.kind = 2;
+        return w;
+    }
+    w.kind = 0;
+    w.lo = w.win.lo;
+    w.hi = w.win.hi;
+    w.n = (w.hi - w.lo + 3) & ~3;
+    w.lo = w.hi - w.n;
+    if (w.lo < 0) { w.hi -= w.lo; w.lo = 0; }
+    w.x = 1.0 + (double)t;
+    w.qi = exp_small(pc.a2);
+    w.G = (double)mu * exp_wide_b(-(double)pc.a2 * ((double)(w.hi - 1) + 0.5 - (double)pc.c));
+    return w;
+}
+
+__device__ inline double delta_ell_direct(float mu, float d, const PixConst& pc, int& nterms) {
+    if (d == 0.0f && mu > 0.0f) return 0.0;
+    const DirectWindow w = direct_window(mu, d, pc);
+    nterms += w.terms;
+    if (w.kind == 1) return __builtin_nan("");
+    if (w.kind == 2) return delta_ell_sharp(d, w.lmu, w.lx, w.win, pc);
     // Four Horner steps acc <- (G_u / n_u)(1 + acc) at a time (n_u = hi - i - u,
     // G_u = G qi^u) over their common denominator N = n0 n1 n2 n3:
     //   acc <- G3 [n2 n1 n0 + G2 (n1 n0 + G1 (n0 + G0 (1 + acc)))] / N,
     // one reciprocal per four terms and no per-term one (every quantity is
     // positive, so nothing cancels).  The terms are those of delta_ell_t's
-    // recurrence; series_kept forms the per-term reciprocals its series needs.
-    double acc0 = 0.0, acc1 = 0.0;
+    // recurrence.
+    double G = w.G, acc0 = 0.0, acc1 = 0.0;
 #pragma unroll 1
-    for (int i = 0; i < n4; i += 4) {
-        const double n0 = (double)(hi - i), n1 = n0 - 1.0, n2 = n0 - 2.0, n3 = n0 - 3.0;   // n3 >= lo + 1 >= 1
+    for (int i = 0; i < w.n; i += 4) {
+        const double n0 = (double)(w.hi - i), n1 = n0 - 1.0, n2 = n0 - 2.0, n3 = n0 - 3.0;   // n3 >= lo + 1 >= 1
         const double p10 = n1 * n0, p210 = n2 * p10, N = n3 * p210;
         double iN = __builtin_amdgcn_rcp(N);
         iN = fma(iN, fma(-N, iN, 1.0), iN);
-        const double g0 = G, g1 = g0 * qi, g2 = g1 * qi, g3 = g2 * qi;
-        G = g3 * qi;
+        const double g0 = G, g1 = g0 * w.qi, g2 = g1 * w.qi, g3 = g2 * w.qi;
+        G = g3 * w.qi;
         double t = fma(g0, acc0, g0) + n0;
         t = fma(g1, t, p10);
         t = fma(g2, t, p210);
         acc0 = (g3 * t) * iN;
-        const double x0 = g0 * x, x1 = g1 * x, x2 = g2 * x, x3 = g3 * x;
+        const double x0 = g0 * w.x, x1 = g1 * w.x, x2 = g2 * w.x, x3 = g3 * w.x;
         t = fma(x0, acc1, x0) + n0;
         t = fma(x1, t, p10);
         t = fma(x2, t, p210);
         acc1 = (x3 * t) * iN;
     }
-    return fma((double)lo, (double)lx, log_ratio(1.0 + acc1, 1.0 + acc0) - (double)d);
+    return fma((double)w.lo, (double)w.lx, log_ratio(1.0 + acc1, 1.0 + acc0) - (double)d);
 }
 
-__device__ inline Series series_kept(const DirectKeep& k, float mu, float d) {
+// Lane permutations within rows of 16 (data-parallel primitives, no LDS).
+template <int CTRL>
+__device__ inline double dpp_d(double v) {
+    const int2 u = __builtin_bit_cast(int2, v);
+    int2 w;
+    w.x = __builtin_amdgcn_update_dpp(0, u.x, CTRL, 0xF, 0xF, false);
+    w.y = __builtin_amdgcn_update_dpp(0, u.y, CTRL, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, w);
+}
+
+__device__ inline double quad_sum(double v) {
+    v += dpp_d<0xB1>(v);      // quad_perm [1,0,3,2]
+    v += dpp_d<0x4E>(v);      // quad_perm [2,3,0,1]
+    return v;
+}
+
+// The series at mu + d over the window of [mu, mu + d], by four lanes (p = lane
+// mod 4, the same arguments in each, the result in each): lane p takes the
+// terms k = lo + p + 4 m.  Its sum over m is one Horner recurrence from the top
+// in u = (1 + v)^4 - 1, normalised at its lowest term (as series_at is at lo),
+//   A(u) <- R_m (1 + u)(1 + A(u)),  R_m = x^4 G_k G_(k+1) G_(k+2) G_(k+3) /
+//   ((k + 1)(k + 2)(k + 3)(k + 4)),
+// one reciprocal for the four factors; then u is expanded in v, the lane's
+// factor (1 + v)^p W_(lo+p) / W_lo applied and the four lanes added.  A window
+// of n terms is n / 4 dependent steps of about 27 issue slots instead of n of 17.
+// With d = 0 it is the series at mu from mu's own window.  b2 > 0 and R = 0 where
+// no series is formed (a rejected window).
+__device__ inline Series series_after(float mu, float d, const PixConst& pc, int p, int& nterms) {
     Series out;
     out.R = 0.0f;
-    out.b = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (k.n4 < 0) return out;
-    const float t = d * fast_rcp(mu);
-    const double x = 1.0 + (double)t;
-    const double qi = exp_small(k.a2);
-    double G = k.G;
+    out.b = no_series();
+    const DirectWindow w = direct_window(mu, d, pc);
+    if (w.kind == 2) return series_sharp(mu + d, w.win, pc.c, pc.a2);
+    if (w.kind != 0) return out;                                    // the same in the four lanes
+    nterms += p == 0 ? w.terms : 0;
+    // (qi^6 <= exp(480), and the weights' ratios stay in double range with lo as
+    // the reference; a factor that underflows belongs to a negligible term, and
+    // gx itself does not)
+    const double q2 = w.qi * w.qi, q4 = q2 * q2, q6 = q4 * q2;
+    // G at the highest index of this lane's first step: hi - 1 for p = 0 (its
+    // top term is hi), hi - 5 + p = top - (4 - p) otherwise
+    double gx = w.x * (p == 0 ? w.G : w.G * (p == 1 ? q2 * w.qi : (p == 2 ? q2 : w.qi)));
+    int m = (w.n >> 2) - (p == 0 ? 1 : 2);
+    double k = (double)(w.lo + p + 4 * m);
     double A0 = 0.0, A1 = 0.0, A2 = 0.0, A3 = 0.0, A4 = 0.0;
 #pragma unroll 1
-    for (int i = 0; i < k.n4; i += 4) {
-        double cv[4];
-        recip4(k.hi - i, cv);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const double r = G * cv[u];
-            G *= qi;
-            const double rx = r * x;
-            const double T0 = A0 + 1.0;
-            A4 = rx * (A4 + A3);
-            A3 = rx * (A3 + A2);
-            A2 = rx * (A2 + A1);
-            A1 = rx * (A1 + T0);
-            A0 = rx * T0;
-        }
+    for (; m >= 0; --m) {
+        const double t = fma(k, k + 5.0, 4.0), den = t * (t + 2.0); // (k + 1)(k + 4) (k + 2)(k + 3)
+        double r = __builtin_amdgcn_rcp(den);
+        r = fma(r, fma(-den, r, 1.0), r);
+        const double g2 = gx * gx, R = (g2 * q6) * (g2 * r);         // x^4 G_k .. G_(k+3) = (x G_(k+3))^4 qi^6
+        gx *= q4;
+        k -= 4.0;
+        const double T0 = A0 + 1.0;
+        A4 = R * (A4 + A3);
+        A3 = R * (A3 + A2);
+        A2 = R * (A2 + A1);
+        A1 = R * (A1 + T0);
+        A0 = R * T0;
     }
-    return series_finish(A0, A1, A2, A3, A4, k.hi - k.n4, mu + d);
+    // u = 4 v + 6 v^2 + 4 v^3 + v^4
+    const double c0 = A0 + 1.0, c1 = 4.0 * A1, c2 = fma(16.0, A2, 6.0 * A1),
+                 c3 = fma(64.0, A3, fma(48.0, A2, 4.0 * A1)),
+                 c4 = fma(256.0, A4, fma(288.0, A3, fma(68.0, A2, A1)));
+    // W_(lo+p) / W_lo: lane 0 ended with x G_(lo+3) qi^4
+    const double gl = dpp_d<0x00>(gx);                              // x G_(lo-1)
+    const double l1 = (double)(w.lo + 1), l2 = l1 + 1.0, l3 = l1 + 2.0;
+    const double l12 = l1 * l2, l123 = l12 * l3;
+    double il = __builtin_amdgcn_rcp(p == 3 ? l123 : (p == 2 ? l12 : l1));
+    il = fma(il, fma(-(p == 3 ? l123 : (p == 2 ? l12 : l1)), il, 1.0), il);
+    const double iq = rcp_nr(w.qi), g1 = gl * iq, g2 = g1 * iq, g3 = g2 * iq;   // x G_lo, x G_(lo+1), x G_(lo+2)
+    const double s = p == 0 ? 1.0 : il * (p == 1 ? g1 : (p == 2 ? g1 * g2 : g1 * g2 * g3));
+    const double b1 = (double)p, b2 = (double)(p == 3 ? 3 : (p == 2 ? 1 : 0)), b3 = p == 3 ? 1.0 : 0.0;
+    const double d0 = c0, d1 = fma(b1, c0, c1), d2 = fma(b2, c0, fma(b1, c1, c2)),
+                 d3 = fma(b3, c0, fma(b2, c1, fma(b1, c2, c3))), d4 = fma(b3, c1, fma(b2, c2, fma(b1, c3, c4)));
+    const double S0 = quad_sum(s * d0), S1 = quad_sum(s * d1), S2 = quad_sum(s * d2), S3 = quad_sum(s * d3),
+                 S4 = quad_sum(s * d4);
+    return series_finish(S0, S1, S2, S3, S4, w.lo, mu + d);
+}
+
+// A term whose move leaves its series' radius: centre and half-width of an
+// interval that holds what the direct evaluation returns.  Anchor m, series
+// coefficients b, displacement D (inside the radius), y = D + d, v = y / m.  With p_j =
+// sum_i beta_i^j (p_1 = E = (1 + b1) m, p_2 = s2 = -2 b2 m^2, p_3 = 3 b3 m^3, p_4 = -4 b4
+// m^4) and T_n the degree-n series of sum_i log(1 + beta_i v), the rest r_n(x) =
+// log(1 + x) - x + ... (degree n) satisfies, term by term since 0 < beta < 1,
+//   v > 0:  beta^4 |r_3(v)| <= |r_3(beta v)| <= beta^3 |r_3(v)|, r_3 < 0, so
+//           T_3 + p_3 r_3(v) <= sum <= T_3 + p_4 r_3(v);
+//   v < 0:  T_4 + p_4 r_4(v) <= sum <= T_4 (r_4 < 0, powers of beta fall);
+// and, with log(1 + beta v) / beta convex and falling in beta, the chord over
+// [0, 1] and Jensen's inequality give for every v > 0, used from v = 1 on,
+//   (E^2 / s2) log(1 + s2 v / E) <= sum <= (E - s2) v + s2 log(1 + v).
+// At D the series is within TAU / 2.  The rounding of the direct evaluation
+// (FP32 logs) and of the coefficients is a few 1e-7 of E |v|, over 1 - |v| for
+// v < 0, that of log(1 + v) here at most 2e-7 of E; 4e-6 and 1e-6 are added.  Infinite where nothing is claimed: no series (b2 > 0), y at the
+// edge of -m, and counts so large that the direct window may be refused.
+struct TermBound { float c, e; };
+
+// sd: series_delta(b, D, y - D).
+__device__ inline TermBound series_bound(float m, float4 b, float D, float y, float sd) {
+    TermBound t;
+    const float v = y * fast_rcp(m), m2 = m * m, v2 = v * v;
+    const float E = fmaf(b.x, m, m), s2 = -2.0f * b.y * m2, p3 = 3.0f * b.z * m2 * m, p4 = -4.0f * b.w * m2 * m2;
+    const float l = fast_ln(1.0f + v);
+    const float r3 = l - v * fmaf(v, fmaf(v, 0.33333333f, -0.5f), 1.0f);
+    const float q4 = 0.25f * v2 * v2;
+    const float up = v > 0.0f ? p3 * r3 + p4 * q4 : 0.0f, lo = p4 * (r3 + q4);
+    t.c = sd + 0.5f * (up + lo);
+    t.e = 0.5f * fabsf(up - lo);
+    const float ay = fabsf(y), cnt = fabsf(b.x) + 1.0f, den = m - ay;
+    float scale = 1.0f;
+    if (v < 0.0f) scale = m * fast_rcp(den);
+    if (v > 1.0f) {
+        const float hi = fmaf(E - s2, v, s2 * l), jn = E * (E * fast_rcp(s2)) * log1p_k(s2 * v * fast_rcp(E));
+        // (no count to speak of: the sum lies in [0, E v])
+        const float lw = E > 1e-15f && s2 > 1e-15f ? jn : 0.0f;
+        t.c = 0.5f * (hi + lw) - y - series_delta(b, 0.0f, D);
+        t.e = 0.5f * fabsf(hi - lw);
+    }
+    t.e = fmaf(cnt * scale, fmaf(4e-6f, ay + fabsf(D), 1e-6f * m), t.e + 1.6e-9f);
+    if (!(b.y <= 0.0f && (v > 0.0f || den > 0.02f * m) && cnt * (m + ay) < 2.5e5f && t.e < INFINITY)) {
+        t.c = 0.0f;
+        t.e = INFINITY;
+    }
+    return t;
 }
 
 // Likelihood change of one footprint pixel for the camera the kernel was
@@ -592,12 +734,13 @@ __device__ inline double delta_pix(float mu, float d, const PixConst& pc, const 
 
 __device__ inline Series series_at(float mu, const PixConst& pc, int& nterms) {
     Series out;
-    out.b = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    out.b = no_series();
     out.R = 0.0f;
-    if (!(mu > 0.0f) || pc.a2 > 2.0f * A_RECUR_MAX || pc.a2 < 0.0f) return out;   // < 0: EMCCD pixel
+    if (!(mu > 0.0f) || pc.a2 < 0.0f) return out;   // < 0: EMCCD pixel
     const float lmu = fast_ln(mu);
     const Window win = phi_window(lmu, lmu, pc);
     if (!win.ok) return out;
+    if (pc.a2 > 2.0f * A_RECUR_MAX) return series_sharp(mu, win, pc.c, pc.a2);
     nterms += win.hi - win.lo + 1;
     // the window widened to a multiple of four terms, as in delta_ell_t
     int lo = win.lo, hi = win.hi;
@@ -626,22 +769,7 @@ __device__ inline Series series_at(float mu, const PixConst& pc, int& nterms) {
             A0 = r * T0;
         }
     }
-    return series_finish(A0, A1, A2, A3, A4, lo, mu);
-}
-
-// Change of the series between displacements y0 = D and y1 = D + d from the
-// anchor, as d times the divided difference of the polynomial (Horner on both
-// points at once), so it stays proportional to d without cancellation.
-__device__ inline float series_delta(float4 b, float D, float d) {
-    const float y1 = D + d;
-    float q = b.w;
-    float p = fmaf(b.w, D, b.z);
-    q = fmaf(q, y1, p);
-    p = fmaf(p, D, b.y);
-    q = fmaf(q, y1, p);
-    p = fmaf(p, D, b.x);
-    q = fmaf(q, y1, p);
-    return d * q;
+    return series_finish(1.0 + A0, A1, A2, A3, A4, lo, mu);
 }
 
 }  // namespace bdc

@@ -45,15 +45,14 @@ struct State {
     float* rho;                    // [C][N]
     float* log_step;               // [C][N]
     float* mu;                     // [C][N]
-    float* prop_rho;               // proposals of the current sweep, [C][N]
-    float* prop_hast;              // log q-ratio + log prior ratio, [C][N]
-    float* prop_logu;              // log of the accept uniform, [C][N]
+    float4* prop;                  // proposals of the current sweep, [C][N]: (rho', log q-ratio + log prior
+                                   // ratio, log of the accept uniform, rho' - rho): one load per update
     int64_t* t;                    // device copy of the sweep index
     unsigned long long* accepts;   // [C]
     unsigned long long* counters;  // [0] phi terms summed, [1] footprint evaluations,
-                                   // [2] direct evaluations, [3] series anchored from scratch,
-                                   // [4] their phi terms, [5] series re-anchored in a direct
-                                   // evaluation (block-series scan)
+                                   // [2] direct evaluations, [3] series anchored (block-series scans:
+                                   // new ring rows, accepted moves out of the radius), [4] their phi
+                                   // terms, [5] unused (0)
 };
 
 struct Prior { int kind; float a, b; };

@@ -17,16 +17,19 @@ namespace bdc {
 
 namespace {
 
-__device__ inline PixConst load_pc(const float4* pc, int64_t n) {
-    // 16-byte records; frames stay below 2^27 pixels, so a 32-bit byte offset
-    // from the base suffices
-    const float4 u = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(pc) + ((uint32_t)n << 4));
+__device__ inline PixConst pc_of(float4 u) {
     PixConst p;
     p.c = u.x; p.a2 = u.y; p.L0 = u.z; p.iB = u.w;
     p.ks = fmaxf(p.c, 0.0f);
     p.inv2a = __builtin_amdgcn_rcpf(p.a2);
     p.h0 = __builtin_amdgcn_sqrtf(2.0f * TAIL_T * p.inv2a);
     return p;
+}
+
+__device__ inline PixConst load_pc(const float4* pc, int64_t n) {
+    // 16-byte records; frames stay below 2^27 pixels, so a 32-bit byte offset
+    // from the base suffices
+    return pc_of(*reinterpret_cast<const float4*>(reinterpret_cast<const char*>(pc) + ((uint32_t)n << 4)));
 }
 
 // Per-pixel constants of the phi window from c and a (see PixConst).
@@ -217,9 +220,8 @@ __device__ inline void propose_cell(const Frame& f, const State& S, const Prior&
     float hast = hs;
     if (pr.kind == 1) hast += (pr.a - 1.0f) * hs - pr.b * (rp - r0);
     if (!(rp > 0.0f) || !isfinite(rp)) hast = -INFINITY;
-    S.prop_rho[i] = rp;
-    S.prop_hast[i] = hast;
-    S.prop_logu[i] = logf(u01(draw(f.key, (uint32_t)m, (uint32_t)t, (uint32_t)chain, STREAM_ACCEPT).x));
+    S.prop[i] = make_float4(rp, hast, logf(u01(draw(f.key, (uint32_t)m, (uint32_t)t, (uint32_t)chain, STREAM_ACCEPT).x)),
+                            rp - r0);
 }
 
 // One FT x FT output tile of one chain.  lds: (FT + 2r)^2 + s^2 floats.
@@ -347,8 +349,8 @@ __device__ inline bool decide_and_commit(const Frame& f, const State& S, int cha
                                          int burn_in, double tot, bool writer,
                                          float* dbg_delta, uint8_t* dbg_acc) {
     const int64_t i = (int64_t)chain * f.N + m;
-    return decide_commit(f, S, chain, m, t, burn_in, tot, writer, S.prop_hast[i], S.prop_logu[i], S.prop_rho[i],
-                         dbg_delta, dbg_acc);
+    const float4 pr = S.prop[i];
+    return decide_commit(f, S, chain, m, t, burn_in, tot, writer, pr.y, pr.z, pr.x, dbg_delta, dbg_acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -379,7 +381,7 @@ __global__ void __launch_bounds__(WG) k_colour_pass(Frame f, State S, int burn_i
     const int chain = blockIdx.y;
     const int64_t m = (int64_t)y * f.W + x;
     const int64_t base = (int64_t)chain * f.N;
-    const float d = S.prop_rho[base + m] - S.rho[base + m];
+    const float d = S.prop[base + m].w;
     const float* mu = S.mu + base;
     double part = 0.0;
     int nterms = 0, nevals = 0;
@@ -427,7 +429,7 @@ __global__ void __launch_bounds__(WG) k_colour_pass_sub(Frame f, State S, int bu
     const int64_t m = (int64_t)(py * k + phase / k) * f.W + (px * k + phase % k);
     const int64_t base = (int64_t)chain * f.N, pbase = (int64_t)chain * f.Np;
     const float* T = f.psf + (int64_t)phase * F;
-    const float d = S.prop_rho[base + m] - S.rho[base + m];
+    const float d = S.prop[base + m].w;
     const float* mu = S.mu + pbase;
     double part = 0.0;
     int nterms = 0, nevals = 0;
@@ -664,10 +666,11 @@ __device__ void block_phase_block(const Frame& f, const State& S, int burn_in, c
         if (nact == 1 && sorted) {
             const int ly = ky, lx = kx;
             const int64_t m = (int64_t)(by0 + ly) * f.W + (bx0 + lx);
-            pre_rp = S.prop_rho[base + m];
-            pre_hast = S.prop_hast[base + m];
-            pre_logu = S.prop_logu[base + m];
-            const float d = pre_rp - S.rho[base + m];
+            const float4 pr = S.prop[base + m];
+            pre_rp = pr.x;
+            pre_hast = pr.y;
+            pre_logu = pr.z;
+            const float d = pr.w;
             if (threadIdx.x == 0) s_d[0] = d;
             const int rbase = ly * RW + lx;
             // counting sort of this wave's evaluations by window class
@@ -749,9 +752,7 @@ __device__ void block_phase_block(const Frame& f, const State& S, int burn_in, c
             for (int a = 0; a < nact; ++a) {
                 const int ly = ky + s * (a / nax), lx = kx + s * (a % nax);
                 const int64_t m = (int64_t)(by0 + ly) * f.W + (bx0 + lx);
-                // rho_m is read before any commit of this colour (the barrier below
-                // orders the reads before thread 0 overwrites it)
-                const float d = S.prop_rho[base + m] - S.rho[base + m];
+                const float d = S.prop[base + m].w;
                 if (threadIdx.x == 0) s_d[a] = d;
                 const int rbase = ly * RW + lx;                   // footprint origin in the region
                 double part = 0.0;
@@ -883,9 +884,7 @@ __global__ void __launch_bounds__(WG) k_block_phase_sub(Frame f, State S, int bu
         for (int a = 0; a < nact; ++a) {
             const int ly = ky + s * (a / nax), lx = kx + s * (a % nax);
             const int64_t m = (int64_t)((by0 + ly) * k + ph / k) * f.W + ((bx0 + lx) * k + ph % k);
-            // rho_m is read before any commit of this colour (the barrier below
-            // orders the reads before thread 0 overwrites it)
-            const float d = S.prop_rho[base + m] - S.rho[base + m];
+            const float d = S.prop[base + m].w;
             if (threadIdx.x == 0) s_d[a] = d;
             const int rbase = ly * RW + lx;                   // footprint origin in the region
             double part = 0.0;
@@ -1032,40 +1031,44 @@ __global__ void __launch_bounds__(WG) k_chunk_fourier(Frame f, State S, MomentBu
 // Moving to the next block row writes the oldest row back to mu and loads the
 // next region row with fresh series.  Each thread holds SER_Q footprint
 // entries, in descending PSF weight: the first (q = 0) covers the PSF core,
-// where relative moves are large, so direct evaluations fall almost only on
-// q = 0 and a wave runs delta_ell about once per update.  That evaluation also
-// forms the series at mu + d, which the lane installs if the move is accepted
-// (|D + d| > R leaves the radius, so the old series is spent).
+// where relative moves are large and terms leave their radius.
+//
+// Decisions.  A term outside its radius still has its series' coefficients, and
+// they give an interval that holds the direct evaluation (series_bound).  The
+// update sums every term's series or interval centre and the half-widths; when
+// log u lies farther from Delta than their sum, the direct evaluations could
+// not change the decision and none is made.  Otherwise (and when Delta itself is asked for)
+// the terms outside are evaluated directly, as a pass without bounds would
+// always do, so the chain is the same bit for bit.  What an update waited for
+// was one dependent chain of direct evaluations on a few lanes; 2048 x 2048, 4
+// chains, Airy 31 x 31: 147.6 to 121.1 ms for two sweeps (17.9 to 14.7 ms per
+// launch), direct evaluations 32 to 0.16 per update; 512 x 512, one chain (one
+// workgroup per CU, all latency): 46.1 to 35.5 ms for four sweeps.
+// An accepted move re-anchors the pixels that left their radius (|D + d| > R:
+// the old series is spent).  Those of the PSF core are queued in LDS with their
+// record before the decision, and after it consecutive threads of one wave take
+// one each, rather than every wave running the whole series for its few lanes;
+// the wave that does it differs between neighbouring blocks.
 // Counters: [0] phi terms of direct evaluations, [1] footprint evaluations,
-// [2] direct evaluations, [3] series anchored from scratch (series_at: new
-// ring rows, rare commits), [4] their phi terms, [5] series re-anchored inside
-// a direct evaluation.
+// [2] direct evaluations, [3] series anchored (new ring rows, accepted moves
+// out of the radius), [4] their phi terms.
 // ---------------------------------------------------------------------------
 constexpr int SER_Q = 4;                      // footprint entries per thread (F <= SER_Q * WG)
+constexpr int SER_JOBS = 48;                  // queued pixels to re-anchor; beyond, the owner lanes
 
-__device__ inline void count_work6(unsigned long long* ctr, int terms, int evals, int direct, int anchors,
-                                   int anchor_terms, int fused) {
-    unsigned long long v[6] = {(unsigned long long)terms, (unsigned long long)evals, (unsigned long long)direct,
-                               (unsigned long long)anchors, (unsigned long long)anchor_terms, (unsigned long long)fused};
+__device__ inline void count_work5(unsigned long long* ctr, int terms, int evals, int direct, int anchors,
+                                   int anchor_terms) {
+    unsigned long long v[5] = {(unsigned long long)terms, (unsigned long long)evals, (unsigned long long)direct,
+                               (unsigned long long)anchors, (unsigned long long)anchor_terms};
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
+    for (int k = 0; k < 5; ++k) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
     }
     if ((threadIdx.x & 63) == 0) {
 #pragma unroll
-        for (int k = 0; k < 6; ++k) atomicAdd(&ctr[k], v[k]);
+        for (int k = 0; k < 5; ++k) atomicAdd(&ctr[k], v[k]);
     }
-}
-
-// Lane permutations within rows of 16 (data-parallel primitives, no LDS).
-template <int CTRL>
-__device__ inline double dpp_d(double v) {
-    const int2 u = __builtin_bit_cast(int2, v);
-    int2 w;
-    w.x = __builtin_amdgcn_update_dpp(0, u.x, CTRL, 0xF, 0xF, false);
-    w.y = __builtin_amdgcn_update_dpp(0, u.y, CTRL, 0xF, 0xF, false);
-    return __builtin_bit_cast(double, w);
 }
 
 __device__ inline double readlane_d(double v, int lane) {
@@ -1077,13 +1080,50 @@ __device__ inline double readlane_d(double v, int lane) {
 }
 
 // Sum over the 64 lanes, the same value in every lane: pairs, quads, half rows
-// and rows by DPP, then the four row sums in a fixed order.
+// and rows by DPP, then rows into the next (row_bcast15, row_bcast31), so that
+// lane 63 holds the sum.
+template <int CTRL, int ROWS>
+__device__ inline double dpp_rows(double v) {
+    const int2 u = __builtin_bit_cast(int2, v);
+    int2 w;
+    w.x = __builtin_amdgcn_update_dpp(0, u.x, CTRL, ROWS, 0xF, false);
+    w.y = __builtin_amdgcn_update_dpp(0, u.y, CTRL, ROWS, 0xF, false);
+    return __builtin_bit_cast(double, w);
+}
+
 __device__ inline double wave_sum_dpp(double v) {
     v += dpp_d<0xB1>(v);      // quad_perm [1,0,3,2]
     v += dpp_d<0x4E>(v);      // quad_perm [2,3,0,1]
     v += dpp_d<0x141>(v);     // row_half_mirror
     v += dpp_d<0x140>(v);     // row_mirror
-    return (readlane_d(v, 0) + readlane_d(v, 16)) + (readlane_d(v, 32) + readlane_d(v, 48));
+    v += dpp_rows<0x142, 0xA>(v);
+    v += dpp_rows<0x143, 0xC>(v);
+    return readlane_d(v, 63);
+}
+
+__device__ inline int lanes_below(uint64_t mask) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+template <int CTRL, int ROWS>
+__device__ inline float dpp_f(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWS, 0xF, false));
+}
+
+__device__ inline float wave_sum_dpp_f(float v) {
+    v += dpp_f<0xB1, 0xF>(v);
+    v += dpp_f<0x4E, 0xF>(v);
+    v += dpp_f<0x141, 0xF>(v);
+    v += dpp_f<0x140, 0xF>(v);
+    v += dpp_f<0x142, 0xA>(v);
+    v += dpp_f<0x143, 0xC>(v);
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+
+// Whether Delta, known to within err (0: exactly), decides against log u: the
+// sums of the two evaluations round apart by far less than the 1e-7 kept.
+__device__ inline bool decided(double delta, float logu, float err) {
+    return err == 0.0f || fabs(delta - (double)logu) > fma(1.02, (double)err, 1e-7);
 }
 
 // LDS ring of one block: per region pixel (slot * RW + x), 28 bytes in three
@@ -1135,16 +1175,82 @@ __device__ inline void series_store_rows(const Frame& f, const State& S, int64_t
     }
 }
 
+// Footprint entry e (in descending PSF weight) of the update at block column lx
+// of block row ly: offset (oy | ox << 8), ring index and the move's change.
+__device__ inline void footprint_entry(const Frame& f, int RW, int ly, int lx, int e, float d0, int& o, int& ri,
+                                       float& dj) {
+    const int s = f.s, j = f.psf_order[e], oy = j / s, ox = j - oy * s;
+    int slot = ly % s + oy;
+    slot = slot >= s ? slot - s : slot;
+    o = oy | ox << 8;
+    ri = slot * RW + ox + lx;
+    dj = d0 * f.psf[j];
+}
+
+// This thread's share of Delta with the terms outside their radius evaluated
+// directly (rare: everything is read again rather than kept for it).
+struct DirectPart { double sum; int terms, n; };
+
+__device__ inline DirectPart block_direct_part(const Frame& f, const Ring& ring, int RW, int ly, int lx,
+                                                     int64_t m, float d0) {
+    const int F = f.s * f.s, r = f.r;
+    DirectPart p = {0.0, 0, 0};
+    float fpart = 0.0f;
+#pragma unroll 1
+    for (int e = threadIdx.x; e < F; e += WG) {
+        int o, i;
+        float dj;
+        footprint_entry(f, RW, ly, lx, e, d0, o, i, dj);
+        const float4 A = ring.A[i];
+        if (!(A.y >= 0.0f)) continue;
+        if (fabsf(A.x + dj) <= A.y) {
+            const float2 Bv = ring.B[i];
+            fpart += series_delta(make_float4(A.z, A.w, Bv.x, Bv.y), A.x, dj);
+        } else {
+            const PixConst pc = load_pc(f.pc, m + (int64_t)((o & 0xFF) - r) * f.W + ((o >> 8) - r));
+            const float mu = ring.ma[i] + A.x;
+            // a thread's first by the grouped recurrence, further ones term by term
+            p.sum += p.n == 0 ? delta_ell_direct(mu, dj, pc, p.terms) : delta_ell_notab(mu, dj, pc, p.terms);
+            ++p.n;
+        }
+    }
+    p.sum += (double)fpart;
+    return p;
+}
+
+// Slots of the re-anchoring queue: up to SER_JOBS, fewer where the ring leaves
+// less room below the LDS size at which one more workgroup fits on a CU (the
+// ring of a 31 x 31 PSF at B = 31 leaves 25).
+constexpr int SER_JOB_BYTES = sizeof(float4) + sizeof(float2) + sizeof(int);
+__host__ __device__ inline size_t block_series_fixed(int B, int s) {
+    const int RW = B + 2 * (s / 2);
+    return (size_t)2 * WAVES * (sizeof(double) + sizeof(float)) + 4 * sizeof(int) +
+           ((size_t)s * RW + 1) * (sizeof(float4) + sizeof(float2) + sizeof(float));
+}
+__host__ __device__ inline int block_series_jobs(int B, int s) {
+    constexpr size_t CU = 160 * 1024, GRAIN = 1280;                // LDS of a CU, its allocation grain
+    const size_t fixed = block_series_fixed(B, s);
+    const size_t room = CU / (CU / ((fixed + 16 * SER_JOB_BYTES + GRAIN - 1) / GRAIN * GRAIN)) / GRAIN * GRAIN;
+    const size_t n = (room - fixed) / SER_JOB_BYTES;
+    return n < SER_JOBS ? (int)n : SER_JOBS;
+}
+
 __device__ void block_series_block(const Frame& f, const State& S, int burn_in, int B,
                                    int py, int px, int bi, int chain, int64_t t, int k0, int k1, float* dbg_delta,
                                    uint8_t* dbg_acc, double* lds_d) {
+    const int cap = block_series_jobs(B, f.s);
     const int s = f.s, r = f.r, F = s * s;
     const int RW = B + 2 * r, NR = s * RW;
     double* s_red = lds_d;                                          // [2][WAVES]
+    float* s_err = reinterpret_cast<float*>(s_red + 2 * WAVES);     // [2][WAVES]
+    int* s_cnt = reinterpret_cast<int*>(s_err + 2 * WAVES);         // [4]: queued pixels, three updates in turn
+    float4* job_pc = reinterpret_cast<float4*>(s_cnt + 4);          // [cap] the queue: per-pixel record,
     Ring ring;
-    ring.A = reinterpret_cast<float4*>(s_red + 2 * WAVES);          // [NR]
-    ring.B = reinterpret_cast<float2*>(ring.A + NR);                // [NR]
-    ring.ma = reinterpret_cast<float*>(ring.B + NR);                // [NR]
+    ring.A = job_pc + cap;                                          // [NR + 1]
+    ring.B = reinterpret_cast<float2*>(ring.A + NR + 1);            // [NR + 1]
+    float2* job_md = ring.B + NR + 1;                               // [cap] (mu, d),
+    ring.ma = reinterpret_cast<float*>(job_md + cap);               // [NR + 1]
+    int* job_ri = reinterpret_cast<int*>(ring.ma + NR + 1);         // [cap] ring index
 
     const int nbx = (f.W + B - 1) / B;
     const int nbx_p = (nbx - px + 1) / 2;
@@ -1167,14 +1273,20 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
         pw[q] = j >= 0 ? f.psf[j] : 0.0f;
     }
     const int oy0 = off[0] & 0xFF, ox0 = (off[0] >> 8) & 0xFF;
-    int nterms = 0, nevals = 0, ndirect = 0, nanch = 0, aterms = 0, nfused = 0;
+    // padding entries (F < SER_Q * WG) read the sink cell: outside the frame
+    if (threadIdx.x == 0) {
+        ring.A[NR] = make_float4(0.0f, -1.0f, 0.0f, 0.0f);
+        ring.B[NR] = make_float2(0.0f, 0.0f);
+        ring.ma[NR] = 0.0f;
+    }
+    int nterms = 0, nevals = 0, ndirect = 0, nanch = 0, aterms = 0;
     // the colours [k0, k1) visit rows ly of the block, columns [lx_lo, lx_hi)
     auto lx_lo = [&](int y) { return max(0, k0 - y * s); };
     auto lx_hi = [&](int y) { return min(bw, k1 - y * s); };
     int ly = k0 / s, lx = lx_lo(ly);
     while (ly < bh && lx >= lx_hi(ly)) { ++ly; lx = lx_lo(ly); }
     if (ly >= bh) {
-        count_work6(S.counters, 0, 0, 0, 0, 0, 0);
+        count_work5(S.counters, 0, 0, 0, 0, 0);
         return;
     }
     int ly_cur = ly;
@@ -1187,23 +1299,23 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
             const int oy = off[q] & 0xFF, ox = (off[q] >> 8) & 0xFF;
             int slot = slot0 + oy;
             slot = slot >= s ? slot - s : slot;
-            rb[q] = off[q] >= 0 ? slot * RW + ox : 0;
+            rb[q] = off[q] >= 0 ? slot * RW + ox : NR;
         }
     };
     row_bases(ly_cur);
     series_load_rows(f, S, base, ry0, rx0, RW, ly_cur, s, ring, aterms, nanch);
+    if (threadIdx.x < 4) s_cnt[threadIdx.x] = 0;
     lds_barrier();
+    // the wave that re-anchors: another one in the next block of a launch
+    const int job0 = ((threadIdx.x + 64 * (bi & (WAVES - 1))) & (WG - 1)) >> 2;
     // inputs of the next update, loaded one update ahead: the decision inputs,
     // and the per-pixel constants of this thread's PSF-core entry (q = 0),
     // where direct evaluations fall
-    float n_rp, n_hast, n_logu, n_rho;
+    float4 n_pr;
     float4 n_pc = make_float4(0.0f, 1.0f, 0.0f, 0.0f);
     auto prefetch = [&](int y, int x) {
         const int64_t i = base + (int64_t)(by0 + y) * f.W + (bx0 + x);
-        n_rp = S.prop_rho[i];
-        n_hast = S.prop_hast[i];
-        n_logu = S.prop_logu[i];
-        n_rho = S.rho[i];
+        n_pr = S.prop[i];
         const int gy = by0 + y + oy0 - r, gx = bx0 + x + ox0 - r;
         if (off[0] >= 0 && gy >= 0 && gy < f.H && gx >= 0 && gx < f.W) n_pc = f.pc[(int64_t)gy * f.W + gx];
     };
@@ -1229,10 +1341,9 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
         if (t < burn_in) S.log_step[i] = row_ls;
     };
     row_begin(ly);
-    int par = 0;
+    int par = 0, cq = 0;
     while (ly < bh) {
-        const float rp = n_rp, hast = n_hast, logu = n_logu;
-        const float d0 = rp - n_rho;
+        const float rp = n_pr.x, hast = n_pr.y, logu = n_pr.z, d0 = n_pr.w;
         const float4 pcv0 = n_pc;
         int nly = ly, nlx = lx + 1;
         while (nly < bh && nlx >= lx_hi(nly)) { ++nly; nlx = lx_lo(nly); }
@@ -1258,91 +1369,89 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
         float2 Bq[SER_Q];
 #pragma unroll
         for (int q = 0; q < SER_Q; ++q) {
-            ri[q] = off[q] >= 0 ? rb[q] + lx : 0;
+            ri[q] = off[q] >= 0 ? rb[q] + lx : NR;
             Aq[q] = ring.A[ri[q]];
             Bq[q] = ring.B[ri[q]];
         }
-        const float ma0 = ring.ma[ri[0]];                           // the PSF-core entry may go direct
-        // 2. series or direct
-        int fast = 0, need = 0;
-        float dq[SER_Q];
+        const float ma0 = ring.ma[ri[0]];                           // the PSF-core entry may leave its radius
+        // 2. every term's series or, outside its radius, its bound.  (A lane's
+        // few terms in FP32: their rounding stays relative to the sum of the
+        // terms' magnitudes.)  A pixel that an accepted move takes out of its
+        // radius is queued: for the PSF core with the record fetched an update
+        // ahead, else with its pixel (marked by a negative 2a).
+        bool fast[SER_Q], any = false;
+        unsigned left = 0;                                          // entries beyond the queue; bit 8: the first is one
+        float y[SER_Q], fpart = 0.0f, gpart = 0.0f, err = 0.0f;
+        // slot i of the queue's round: (mu, d) for a lane's first such pixel,
+        // re-anchored over the window of its move, (mu + d, 0) for further ones,
+        // over that of the new mean
+        auto queue = [&](int q, int i, float mu, float dq, bool first) {
+            const int pix = (int)m + ((off[q] & 0xFF) - r) * f.W + ((off[q] >> 8) - r);
+            job_pc[i] = make_float4(__int_as_float(pix), -2.0f, 0.0f, 0.0f);
+            job_md[i] = first ? make_float2(mu, dq) : make_float2(mu + dq, 0.0f);
+            job_ri[i] = ri[q];
+        };
 #pragma unroll
         for (int q = 0; q < SER_Q; ++q) {
-            dq[q] = d0 * pw[q];
-            if (off[q] >= 0 && Aq[q].y >= 0.0f) {
-                ++nevals;
-                if (fabsf(Aq[q].x + dq[q]) <= Aq[q].y) fast |= 1 << q;
-                else need |= 1 << q;
-            }
-        }
-        double part = 0.0;
-        // 3. direct terms first (the critical path).  Each lane's first direct
-        // entry runs in one pass over the wave, which keeps its window's
-        // recurrence state for the series at mu + d, formed after the decision
-        // if the move is accepted; a lane's further direct entries (rare)
-        // follow.  The PSF-core entry (q = 0) has its per-pixel record
-        // prefetched.
-        DirectKeep dk;
-        dk.n4 = -1;
-        const int rest = need & (need - 1);                         // all but the first
-        float mu_s = 0.0f, d_s = 0.0f;
-        int ri_s = 0;
-        if (need) {
-            // the lowest set bit of need: an entry classified direct, so valid
-            // and inside the frame
-            const int qs = __builtin_ctz((unsigned)need);
-            int off_s = off[0];
-            float D_s = Aq[0].x;
-            d_s = dq[0];
-            ri_s = ri[0];
-#pragma unroll
-            for (int q = 1; q < SER_Q; ++q) {
-                if (q == qs) {
-                    off_s = off[q];
-                    D_s = Aq[q].x;
-                    d_s = dq[q];
-                    ri_s = ri[q];
+            const float dq = d0 * pw[q];
+            y[q] = Aq[q].x + dq;
+            const bool valid = Aq[q].y >= 0.0f;
+            fast[q] = fabsf(y[q]) <= Aq[q].y;
+            const float4 b = make_float4(Aq[q].z, Aq[q].w, Bq[q].x, Bq[q].y);
+            nevals += valid ? 1 : 0;
+            const float sd = series_delta(b, Aq[q].x, dq);
+            if (fast[q]) fpart += sd;
+            const bool need = valid && !fast[q];
+            const uint64_t bal = __ballot(need);
+            if (bal) {
+                int first = 0;
+                if (lane == 0) first = atomicAdd(&s_cnt[cq], __popcll(bal));
+                const float ma = q == 0 ? ma0 : ring.ma[ri[q]];
+                if (need) {
+                    const TermBound tb = series_bound(ma, b, Aq[q].x, y[q], sd);
+                    gpart += tb.c;
+                    err += tb.e;
                 }
-            }
-            PixConst pcs;
-            if (need & 1) {
-                mu_s = ma0 + D_s;
-                pcs.c = pcv0.x; pcs.a2 = pcv0.y; pcs.L0 = pcv0.z; pcs.iB = pcv0.w;
-                pcs.ks = fmaxf(pcs.c, 0.0f);
-                pcs.inv2a = __builtin_amdgcn_rcpf(pcs.a2);
-                pcs.h0 = __builtin_amdgcn_sqrtf(2.0f * TAIL_T * pcs.inv2a);
-            } else {
-                mu_s = ring.ma[ri_s] + D_s;
-                const int oy = off_s & 0xFF, ox = off_s >> 8;
-                pcs = load_pc(f.pc, m + (int64_t)(oy - r) * f.W + (ox - r));
-            }
-            part += delta_ell_keep(mu_s, d_s, pcs, nterms, dk);
-        }
-        if (rest) {
-#pragma unroll
-            for (int q = 1; q < SER_Q; ++q) {
-                if ((rest >> q) & 1) {
-                    const int oy = off[q] & 0xFF, ox = off[q] >> 8;
-                    part += delta_ell_notab(ring.ma[ri[q]] + Aq[q].x, dq[q],
-                                            load_pc(f.pc, m + (int64_t)(oy - r) * f.W + (ox - r)), nterms);
+                first = __builtin_amdgcn_readfirstlane(first) + lanes_below(bal);
+                if (need) {
+                    if (first < cap) {
+                        queue(q, first, ma + Aq[q].x, dq, !any);
+                        if (q == 0) job_pc[first] = pcv0;
+                    } else left |= any ? 1u << q : 0x100u | 1u << q;
+                    any = true;
                 }
             }
         }
-        // 4. series terms (this lane's few in FP32: their rounding stays
-        // relative to the sum of the terms' magnitudes)
-        float fpart = 0.0f;
-#pragma unroll
-        for (int q = 0; q < SER_Q; ++q)
-            if ((fast >> q) & 1) fpart += series_delta(make_float4(Aq[q].z, Aq[q].w, Bq[q].x, Bq[q].y), Aq[q].x, dq[q]);
-        part += (double)fpart;
-        ndirect += __popc(need);
-        part = wave_sum_dpp(part);
-        if (lane == 0) s_red[par * WAVES + wave] = part;
+        const int cq1 = cq == 2 ? 0 : cq + 1;
+        if (threadIdx.x == 0) s_cnt[cq1] = 0;                       // read last before the previous update's barrier
+        double part = wave_sum_dpp((double)fpart + (double)gpart);
+        if (__any(err != 0.0f)) err = wave_sum_dpp_f(err);
+        if (lane == 0) {
+            s_red[par * WAVES + wave] = part;
+            s_err[par * WAVES + wave] = err;
+        }
         lds_barrier();
         double tot = 0.0;
+        float etot = 0.0f;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) tot += s_red[par * WAVES + w];
+        for (int w = 0; w < WAVES; ++w) {
+            tot += s_red[par * WAVES + w];
+            etot += s_err[par * WAVES + w];
+        }
         par ^= 1;
+        // 4. too close to call (or Delta asked for): the direct evaluations
+        if (!decided(tot + (double)hast, logu, etot) || (dbg_delta && etot != 0.0f)) {
+            const DirectPart dp = block_direct_part(f, ring, RW, ly, lx, m, d0);
+            nterms += dp.terms;
+            ndirect += dp.n;
+            part = wave_sum_dpp(dp.sum);
+            if (lane == 0) s_red[par * WAVES + wave] = part;
+            lds_barrier();
+            tot = 0.0;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) tot += s_red[par * WAVES + w];
+            par ^= 1;
+        }
         // the decision (identical in every thread)
         const double delta = tot + (double)hast;
         const bool acc = isfinite(delta) && ((double)logu < delta);
@@ -1360,41 +1469,55 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
         }
         if (acc) {
 #pragma unroll
-            for (int q = 0; q < SER_Q; ++q) {
-                if ((fast >> q) & 1) ring.A[ri[q]].x = Aq[q].x + dq[q];
-            }
-            // direct cases left their series' radius: re-anchor at the new mean
-            if (need && d_s != 0.0f) {
-                const Series nx = series_kept(dk, mu_s, d_s);
-                ring.A[ri_s] = make_float4(0.0f, nx.R, nx.b.x, nx.b.y);
-                ring.B[ri_s] = make_float2(nx.b.z, nx.b.w);
-                ring.ma[ri_s] = mu_s + d_s;
-                ++nfused;
-            }
-#pragma unroll
-            for (int q = 1; q < SER_Q; ++q) {
-                if (((rest >> q) & 1) && dq[q] != 0.0f) {
-                    const int oy = off[q] & 0xFF, ox = off[q] >> 8;
-                    const float mu1 = (ring.ma[ri[q]] + Aq[q].x) + dq[q];
-                    const Series sr = series_at(mu1, load_pc(f.pc, m + (int64_t)(oy - r) * f.W + (ox - r)), aterms);
-                    ring.A[ri[q]] = make_float4(0.0f, sr.R, sr.b.x, sr.b.y);
-                    ring.B[ri[q]] = make_float2(sr.b.z, sr.b.w);
-                    ring.ma[ri[q]] = mu1;
-                    ++nanch;
+            for (int q = 0; q < SER_Q; ++q)
+                if (fast[q]) ring.A[ri[q]].x = y[q];
+            // pixels that left their series' radius: re-anchor at the new mean
+            auto anchor = [&](int i, const Series& nx, float mu1) {
+                ring.A[i] = make_float4(0.0f, nx.R, nx.b.x, nx.b.y);
+                ring.B[i] = make_float2(nx.b.z, nx.b.w);
+                ring.ma[i] = mu1;
+                ++nanch;
+            };
+            // (more than the queue holds, on bright frames: in rounds)
+            for (int n = s_cnt[cq], n0 = 0;;) {
+                if (job0 < min(n - n0, cap)) {
+                    const float2 md = job_md[job0];
+                    float4 rec = job_pc[job0];
+                    if (rec.y == -2.0f) rec = f.pc[__float_as_int(rec.x)];
+                    const Series nx = series_after(md.x, md.y, pc_of(rec), threadIdx.x & 3, aterms);
+                    if ((threadIdx.x & 3) == 0) anchor(job_ri[job0], nx, md.x + md.y);
                 }
+                n0 += cap;
+                if (n <= n0) break;
+                if (threadIdx.x == 0) s_cnt[3] = 0;
+                lds_barrier();
+#pragma unroll
+                for (int q = 0; q < SER_Q; ++q) {
+                    const uint64_t bal = __ballot((left >> q) & 1);
+                    if (!bal) continue;
+                    int i = 0;
+                    if (lane == 0) i = atomicAdd(&s_cnt[3], __popcll(bal));
+                    i = __builtin_amdgcn_readfirstlane(i) + lanes_below(bal);
+                    if (((left >> q) & 1) && i < cap) {
+                        queue(q, i, ring.ma[ri[q]] + ring.A[ri[q]].x, d0 * pw[q], left & 0x100);
+                        left &= ~(0x100u | 1u << q);
+                    }
+                }
+                lds_barrier();
             }
             lds_barrier();                                          // commits before the next footprint reads
         }
+        cq = cq1;
         ly = nly;
         lx = nlx;
     }
     row_end();
     if (threadIdx.x == 0) atomicAdd(&S.accepts[chain], n_acc);
     series_store_rows(f, S, base, ry0, rx0, RW, ly_cur, s, ring);
-    count_work6(S.counters, nterms, nevals, ndirect, nanch, aterms, nfused);
+    count_work5(S.counters, nterms, nevals, ndirect, nanch, aterms);
 }
 
-__global__ void __launch_bounds__(WG) k_block_series(Frame f, State S, int burn_in, int B,
+__global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3))) k_block_series(Frame f, State S, int burn_in, int B,
                                                      int py, int px, int k0, int k1, float* dbg_delta,
                                                      uint8_t* dbg_acc, int nblk) {
     extern __shared__ double lds_d[];
@@ -1417,10 +1540,17 @@ __global__ void __launch_bounds__(WG) k_block_series(Frame f, State S, int burn_
 // every entry's (c, 2a) one update ahead, queues them with the term, and the
 // evaluating lane derives the window constants L0 and iB from them (the
 // window bracket holds for whatever (c, a) the summands use).  Terms,
-// decisions and commits are those of the block-series pass.
+// decisions (by bounds) and commits are those of the block-series pass; here the
+// queue holds every term outside its radius, the bounds are taken one per lane
+// from it, and four lanes re-anchor each pixel of an accepted move.  701 x 1003,
+// Gaussian 15 x 15, 2 chains: 27.9 to 22.0 ms for six sweeps.
 // ---------------------------------------------------------------------------
 constexpr int WS_NQ = 16;                       // footprint entries per lane (F <= 1024)
-constexpr int WS_QCAP = 48;                     // queued direct terms per update; beyond, the owner lanes
+// queued terms per update (beyond, the owner lanes): one per lane for the ring of
+// a 31 x 31 PSF, which fills a quarter of a CU's LDS; two for the smaller ones
+constexpr int ws_cap(int nq) { return nq > 8 ? 64 : 128; }
+constexpr int WS_MOVE = 48;                     // these re-anchor over the window of their move, further ones
+                                                // over that of the new mean
 
 __device__ inline PixConst pc_from(float c, float a2) {
     PixConst pc;
@@ -1435,22 +1565,19 @@ __device__ inline PixConst pc_from(float c, float a2) {
     return pc;
 }
 
-__device__ inline int lanes_below(uint64_t mask) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
-
 template <int NQ>
 __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, int B, int py, int px, int bi,
                                   int chain, int64_t t, int k0, int k1, float* dbg_delta, uint8_t* dbg_acc,
                                   double* lds_d) {
+    constexpr int QCAP = ws_cap(NQ);
     const int s = f.s, r = f.r, F = s * s;
     const int RW = B + 2 * r, NR = s * RW;
-    // queue slot WS_QCAP and ring cell NR are write sinks: lanes with nothing
+    // queue slot QCAP and ring cell NR are write sinks: lanes with nothing
     // to queue or commit write there, so the per-entry steps need no branches
-    float4* jobs = reinterpret_cast<float4*>(lds_d);                // [WS_QCAP + 1]: (mu, d, c, 2a)
-    int* job_ri = reinterpret_cast<int*>(jobs + WS_QCAP + 1);       // [WS_QCAP + 1]: ring index
+    float4* jobs = reinterpret_cast<float4*>(lds_d);                // [QCAP + 1]: (mu, d, c, 2a)
+    int* job_ri = reinterpret_cast<int*>(jobs + QCAP + 1);       // [QCAP + 1]: ring index
     Ring ring;
-    ring.A = reinterpret_cast<float4*>(job_ri + WS_QCAP + 1);       // [NR + 1]
+    ring.A = reinterpret_cast<float4*>(job_ri + QCAP + 4);       // [NR + 1], 16-byte aligned
     ring.B = reinterpret_cast<float2*>(ring.A + NR + 1);            // [NR + 1]
     ring.ma = reinterpret_cast<float*>(ring.B + NR + 1);            // [NR + 1]
 
@@ -1477,13 +1604,13 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
         off[q] = j >= 0 ? ((j / s) | ((j % s) << 8)) : -1;
         pw[q] = j >= 0 ? f.psf[j] : 0.0f;
     }
-    int nterms = 0, nevals = 0, ndirect = 0, nanch = 0, aterms = 0, nfused = 0;
+    int nterms = 0, nevals = 0, ndirect = 0, nanch = 0, aterms = 0;
     auto lx_lo = [&](int y) { return max(0, k0 - y * s); };
     auto lx_hi = [&](int y) { return min(bw, k1 - y * s); };
     int ly = k0 / s, lx = lx_lo(ly);
     while (ly < bh && lx >= lx_hi(ly)) { ++ly; lx = lx_lo(ly); }
     if (ly >= bh) {
-        count_work6(S.counters, 0, 0, 0, 0, 0, 0);
+        count_work5(S.counters, 0, 0, 0, 0, 0);
         return;
     }
     int ly_cur = ly;
@@ -1508,7 +1635,7 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
     // and every entry's (c, 2a), through a buffer resource whose range check
     // turns the reads of entries outside the frame into zeros (such entries
     // have invalid ring records and are never queued)
-    float n_rp, n_hast, n_logu, n_rho;
+    float4 n_pr;
     float2 pcq[NQ];
     const __amdgpu_buffer_rsrc_t pc_rsrc =
         __builtin_amdgcn_make_buffer_rsrc((void*)f.pc, 0, (int)(f.N * (int64_t)sizeof(float4)), 0x00020000);
@@ -1516,10 +1643,7 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
     (void)row_stride;
     auto prefetch = [&](int y, int x) {
         const int64_t m = (int64_t)(by0 + y) * f.W + (bx0 + x);
-        n_rp = S.prop_rho[base + m];
-        n_hast = S.prop_hast[base + m];
-        n_logu = S.prop_logu[base + m];
-        n_rho = S.rho[base + m];
+        n_pr = S.prop[base + m];
         const int m0 = (int)m - r * (f.W + 1);                      // the footprint's top-left pixel
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
@@ -1549,8 +1673,7 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
     };
     row_begin(ly);
     while (ly < bh) {
-        const float rp = n_rp, hast = n_hast, logu = n_logu;
-        const float d0 = rp - n_rho;
+        const float rp = n_pr.x, hast = n_pr.y, logu = n_pr.z, d0 = n_pr.w;
         int nly = ly, nlx = lx + 1;
         while (nly < bh && nlx >= lx_hi(nly)) { ++nly; nlx = lx_lo(nly); }
         if (ly != row_y) {
@@ -1598,13 +1721,12 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
                 fast |= in_r ? 1u << q : 0u;
                 const bool dir = valid && !in_r;
                 nevals += valid ? 1 : 0;
-                ndirect += dir ? 1 : 0;
                 const uint64_t bal = __ballot(dir);
                 if (bal) {
                     const int slot = nq + lanes_below(bal);
-                    const bool queued = dir && slot < WS_QCAP;
+                    const bool queued = dir && slot < QCAP;
                     over |= (dir && !queued) ? 1u << q : 0u;
-                    const int ws = queued ? slot : WS_QCAP;
+                    const int ws = queued ? slot : QCAP;
                     jobs[ws] = make_float4(maq[u] + Aq[u].x, dq, pcq[q].x, pcq[q].y);
                     job_ri[ws] = ring_index(q);
                     nq += __popcll(bal);
@@ -1618,21 +1740,6 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
         // depend on this commit; the footprint records are per frame)
         if (nly < bh) prefetch(nly, nlx);
         wave_fence();
-        // 2. the queued terms, one per lane, each keeping its window's
-        //    recurrence state for the series at its new mean, formed after the
-        //    decision if the move is accepted
-        double part = (double)fpart;
-        DirectKeep dk;
-        dk.n4 = -1;
-        float mu_j = 0.0f, d_j = 0.0f;
-        int ri_j = NR;
-        if (lane < min(nq, WS_QCAP)) {
-            const float4 jb = jobs[lane];
-            mu_j = jb.x;
-            d_j = jb.y;
-            ri_j = job_ri[lane];
-            part += delta_ell_keep(mu_j, d_j, pc_from(jb.z, jb.w), nterms, dk);
-        }
         // terms beyond the queue (rare): their owners, one entry at a time,
         // each rebuilt from the PSF order and the ring
         auto over_entry = [&](int q, int& ri, float& dq, int64_t& pix) {
@@ -1644,19 +1751,52 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
             dq = d0 * f.psf[j];
             pix = m + (int64_t)(oy - r) * f.W + (ox - r);
         };
-        if (nq > WS_QCAP) {
+        // 2. Delta from every term's series; too close to call within the bounds
+        // of those outside their radius (or Delta asked for): the queued terms
+        // evaluated directly, one per lane, then those beyond the queue
+        double part = (double)fpart;
+        float err = 0.0f;
+        if (nq > 0) {
 #pragma unroll 1
-            for (int q = 0; q < NQ; ++q) {
-                if ((over >> q) & 1) {
-                    int ri;
-                    float dq;
-                    int64_t pix;
-                    over_entry(q, ri, dq, pix);
-                    part += delta_ell_notab(ring.ma[ri] + ring.A[ri].x, dq, load_pc(f.pc, pix), nterms);
-                }
+            for (int j = lane; j < min(nq, QCAP); j += 64) {
+                const float4 jb = jobs[j];
+                const int i = job_ri[j];
+                const float4 A = ring.A[i];
+                const float2 Bv = ring.B[i];
+                const float4 b = make_float4(A.z, A.w, Bv.x, Bv.y);
+                const TermBound tb = series_bound(ring.ma[i], b, A.x, A.x + jb.y, series_delta(b, A.x, jb.y));
+                part += (double)tb.c;
+                err += tb.e;
             }
+            if (nq > QCAP) err = INFINITY;
+            err = wave_sum_dpp_f(err);
         }
         part = wave_sum_dpp(part);
+        if (nq > 0) {
+            if (!decided(part + (double)hast, logu, err) || dbg_delta) {
+                part = (double)fpart;
+#pragma unroll 1
+                for (int j = lane; j < min(nq, QCAP); j += 64) {
+                    const float4 jb = jobs[j];
+                    part += delta_ell_direct(jb.x, jb.y, pc_from(jb.z, jb.w), nterms);
+                    ++ndirect;
+                }
+                if (nq > QCAP) {
+#pragma unroll 1
+                    for (int q = 0; q < NQ; ++q) {
+                        if ((over >> q) & 1) {
+                            int ri;
+                            float dq;
+                            int64_t pix;
+                            over_entry(q, ri, dq, pix);
+                            part += delta_ell_notab(ring.ma[ri] + ring.A[ri].x, dq, load_pc(f.pc, pix), nterms);
+                            ++ndirect;
+                        }
+                    }
+                }
+                part = wave_sum_dpp(part);
+            }
+        }
         // the decision (identical in every lane)
         const double delta = part + (double)hast;
         const bool acc = isfinite(delta) && ((double)logu < delta);
@@ -1677,14 +1817,21 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
             for (int q = 0; q < NQ; ++q)
                 ring.A[ring_index(q)].x = ((fast >> q) & 1) ? Dq[q] + d0 * pw[q] : Dq[q];
             // queued terms left their series' radius: re-anchor at the new mean
-            const bool reanchor = ri_j != NR && d_j != 0.0f;
-            const Series nx = series_kept(dk, mu_j, d_j);
-            const int wr = reanchor ? ri_j : NR;
-            ring.A[wr] = reanchor ? make_float4(0.0f, nx.R, nx.b.x, nx.b.y) : make_float4(0.0f, -1.0f, 0.0f, 0.0f);
-            ring.B[wr] = make_float2(nx.b.z, nx.b.w);
-            ring.ma[wr] = mu_j + d_j;
-            nfused += reanchor ? 1 : 0;
-            if (nq > WS_QCAP) {
+#pragma unroll 1
+            for (int j = lane >> 2; j < min(nq, QCAP); j += 16) {
+                const float4 jb = jobs[j];
+                const bool move = j < WS_MOVE;
+                const Series nx = series_after(move ? jb.x : jb.x + jb.y, move ? jb.y : 0.0f, pc_from(jb.z, jb.w),
+                                               lane & 3, aterms);
+                if ((lane & 3) == 0) {
+                    const int i = job_ri[j];
+                    ring.A[i] = make_float4(0.0f, nx.R, nx.b.x, nx.b.y);
+                    ring.B[i] = make_float2(nx.b.z, nx.b.w);
+                    ring.ma[i] = jb.x + jb.y;
+                    ++nanch;
+                }
+            }
+            if (nq > QCAP) {
 #pragma unroll 1
                 for (int q = 0; q < NQ; ++q) {
                     if ((over >> q) & 1) {
@@ -1711,7 +1858,7 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
     row_end();
     if (lane == 0) atomicAdd(&S.accepts[chain], n_acc);
     series_store_rows<64>(f, S, base, ry0, rx0, RW, ly_cur, s, ring);
-    count_work6(S.counters, nterms, nevals, ndirect, nanch, aterms, nfused);
+    count_work5(S.counters, nterms, nevals, ndirect, nanch, aterms);
 }
 
 template <int NQ>
@@ -2288,8 +2435,7 @@ hipError_t launch_chunk_logprior(const Frame& f, const State& S, const MomentBuf
 }
 
 size_t block_series_lds(int B, int s) {
-    const int RW = B + 2 * (s / 2);
-    return (size_t)2 * (WG / 64) * sizeof(double) + (size_t)s * RW * (sizeof(float4) + sizeof(float2) + sizeof(float));
+    return block_series_fixed(B, s) + (size_t)block_series_jobs(B, s) * SER_JOB_BYTES;
 }
 
 bool block_series_fits(int B, int s) {
@@ -2298,7 +2444,8 @@ bool block_series_fits(int B, int s) {
 
 size_t wave_series_lds(int B, int s) {
     const int RW = B + 2 * (s / 2);
-    return (WS_QCAP + 1) * (sizeof(float4) + sizeof(int)) +
+    const int cap = ws_cap((s * s + 63) / 64);
+    return (cap + 1) * sizeof(float4) + (cap + 4) * sizeof(int) +
            ((size_t)s * RW + 1) * (sizeof(float4) + sizeof(float2) + sizeof(float));
 }
 

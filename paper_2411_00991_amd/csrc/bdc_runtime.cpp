@@ -87,7 +87,7 @@ struct bdc_ctx {
     float *d_w = nullptr, *d_gain = nullptr, *d_off = nullptr, *d_sig = nullptr;
     double* d_inv = nullptr;
     float *d_rho = nullptr, *d_ls = nullptr, *d_mu = nullptr;
-    float *d_prho = nullptr, *d_phast = nullptr, *d_plogu = nullptr;
+    float4* d_prop = nullptr;
     int64_t* d_t = nullptr;
     unsigned long long* d_acc = nullptr;
     float *d_mean = nullptr, *d_m2 = nullptr, *d_batch = nullptr;
@@ -100,7 +100,7 @@ struct bdc_ctx {
     float* d_dbg_delta = nullptr;    // C*N, lazily
     uint8_t* d_dbg_acc = nullptr;
 
-    unsigned long long* d_ctr = nullptr;  // [0] phi terms, [1] footprint evaluations, [2] direct, [3] anchors, [4] anchor terms, [5] fused anchors
+    unsigned long long* d_ctr = nullptr;  // [0] phi terms, [1] footprint evaluations, [2] direct, [3] anchors, [4] anchor terms
 
     // learned part: block-proposal maps, block-move counters
     float *d_pm = nullptr, *d_ps = nullptr;
@@ -140,7 +140,7 @@ struct bdc_ctx {
     State state() const {
         State S;
         S.rho = d_rho; S.log_step = d_ls; S.mu = d_mu;
-        S.prop_rho = d_prho; S.prop_hast = d_phast; S.prop_logu = d_plogu;
+        S.prop = d_prop;
         S.t = d_t; S.accepts = d_acc; S.counters = d_ctr;
         return S;
     }
@@ -183,8 +183,8 @@ struct bdc_ctx {
     void free_all() {
         clear_marks();
         drop_graph();
-        void* ptrs[] = {d_psf, d_psf_order, d_pc, d_w, d_gain, d_off, d_sig, d_inv, d_rho, d_ls, d_mu, d_prho, d_phast,
-                        d_plogu, d_t, d_acc, d_mean, d_m2, d_batch, d_lp, d_trace, d_bad, d_tmp, d_tmp2,
+        void* ptrs[] = {d_psf, d_psf_order, d_pc, d_w, d_gain, d_off, d_sig, d_inv, d_rho, d_ls, d_mu, d_prop,
+                        d_t, d_acc, d_mean, d_m2, d_batch, d_lp, d_trace, d_bad, d_tmp, d_tmp2,
                         d_tmpd, d_hist, d_dbg_delta, d_dbg_acc, d_ctr, d_pm, d_ps, d_scale, d_bacc,
                         d_bdbg, d_bdbg_acc, d_dir_am1, d_dir_const, d_dir_F, d_dir_part, d_samples, d_probs,
                         d_qout};
@@ -568,9 +568,7 @@ bdc_status bdc_create(const bdc_config* cfg, void* hip_stream, bdc_ctx** out) {
         c->d_rho = dalloc<float>(CN);
         c->d_ls = dalloc<float>(CN);
         c->d_mu = dalloc<float>((size_t)c->C * c->Np);
-        c->d_prho = dalloc<float>(CN);
-        c->d_phast = dalloc<float>(CN);
-        c->d_plogu = dalloc<float>(CN);
+        c->d_prop = dalloc<float4>(CN);
         c->d_t = dalloc<int64_t>(1);
         c->d_acc = dalloc<unsigned long long>(c->C);
         c->d_mean = dalloc<float>(CN);
@@ -726,8 +724,8 @@ bdc_status bdc_init(bdc_ctx* c, const float* image, const float* rho0, int32_t o
             if (on_device) {
                 r0 = rho0;
             } else {
-                hipck(hipMemcpyAsync(c->d_prho, rho0, CN * sizeof(float), hipMemcpyHostToDevice, c->work), "upload rho0");
-                r0 = c->d_prho;
+                hipck(hipMemcpyAsync(c->d_prop, rho0, CN * sizeof(float), hipMemcpyHostToDevice, c->work), "upload rho0");
+                r0 = reinterpret_cast<const float*>(c->d_prop);
             }
         }
         hipck(launch_init_state(f, c->state(), r0, c->cfg.log_step0, c->d_bad + 2, c->work), "init_state");

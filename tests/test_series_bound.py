@@ -126,3 +126,32 @@ def test_radius_formula_keeps_error_below_tau():
         series = sum(b[j] * y ** (j + 1) for j in range(J))
         slack = 1e-13 * (1.0 + np.abs(ell(c, a, mu)[0]))
         assert np.all(np.abs(exact - series) <= 0.5 * tau + slack)
+
+
+def log_moment_intervals(c, a, mu, v):
+    """(lower, upper) of log E[(1 + v)^phi] from p_j = sum_i beta_i^j, as the scans bound a term
+    outside its radius: the cubic's rest for v > 0, the quartic's for v < 0, and chord and
+    Jensen's inequality in beta for large v."""
+    b, _ = taylor_coefficients(c, a, mu)
+    e, s2, p3, p4 = (b[0] + 1.0) * mu, -2.0 * b[1] * mu ** 2, 3.0 * b[2] * mu ** 3, -4.0 * b[3] * mu ** 4
+    t3 = e * v - s2 * v ** 2 / 2 + p3 * v ** 3 / 3
+    t4 = t3 - p4 * v ** 4 / 4
+    r3 = np.log1p(v) - v + v ** 2 / 2 - v ** 3 / 3
+    r4 = r3 + v ** 4 / 4
+    cubic = np.where(v > 0, t3 + p3 * r3, t4 + p4 * r4), np.where(v > 0, t3 + p4 * r3, t4)
+    if np.any(v < 0):
+        return [cubic]
+    return [cubic, (e * e / s2 * np.log1p(s2 * v / e), (e - s2) * v + s2 * np.log1p(v))]
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("c,a,mu", CASES)
+def test_intervals_outside_the_radius(c, a, mu, sign):
+    """Every interval holds the oracle's exact change (the kernel adds rounding on top)."""
+    v = sign * np.concatenate([np.linspace(0.004, 0.97, 80)] + ([np.geomspace(1.0, 40.0, 30)] if sign > 0 else []))
+    base = ell(c, a, mu)[0]
+    exact = ell(c, a, mu + v * mu) - base + v * mu
+    slack = 1e-12 * (1.0 + abs(base) + np.abs(exact) + mu * np.abs(v)) + 1e-11 * mu * np.abs(v) ** 4
+    for lower, upper in log_moment_intervals(c, a, mu, v):
+        assert np.all(exact >= lower - slack), (exact - lower).min()
+        assert np.all(exact <= upper + slack), (upper - exact).min()
