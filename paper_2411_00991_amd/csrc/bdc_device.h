@@ -71,6 +71,19 @@ struct PixConst {
     float ks, L0, iB, h0;
 };
 
+// Sums that are rounded by themselves.  The compiler may fuse a product into a
+// sum or not, differently in each kernel and version of the source; where a
+// chain's state or decision depends on it, the code says which (these or fmaf),
+// so that the same inputs give the same chain.
+__device__ inline float add_rn(float a, float b) {
+#pragma clang fp contract(off)
+    return a + b;
+}
+__device__ inline float mul_rn(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
+
 __device__ inline float fast_ln(float x) { return __builtin_amdgcn_logf(x) * 0.69314718055994531f; }
 __device__ inline float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
@@ -503,18 +516,18 @@ __device__ inline double delta_ell_notab(float mu, float d, const PixConst& pc, 
 
 // Change of the series between displacements y0 = D and y1 = D + d from the
 // anchor, as d times the divided difference of the polynomial (Horner on both
-// points at once), so it stays proportional to d without cancellation.
-__device__ inline float series_delta(float4 b, float D, float d) {
-    const float y1 = D + d;
+// points at once), so it stays proportional to d without cancellation:
+// d series_slope(b, D, y1).
+__device__ inline float series_slope(float4 b, float D, float y1) {
     float q = b.w;
     float p = fmaf(b.w, D, b.z);
     q = fmaf(q, y1, p);
     p = fmaf(p, D, b.y);
     q = fmaf(q, y1, p);
     p = fmaf(p, D, b.x);
-    q = fmaf(q, y1, p);
-    return d * q;
+    return fmaf(q, y1, p);
 }
+__device__ inline float series_delta(float4 b, float D, float d) { return d * series_slope(b, D, D + d); }
 
 // The direct evaluation of the block-series scans, and the series an accepted
 // move's pixel takes when it leaves its radius.  Both run over one window, that

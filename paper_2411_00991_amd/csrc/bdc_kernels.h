@@ -15,6 +15,7 @@ struct Frame {                     // one frame (or one tile of a batch)
     int64_t N;                     // H * W: object cells (rho, its moments and draws)
     int C;                         // chains
     const float* psf;              // [s*s], sums to 1
+    const double* psf64;           // [2][s*s] column by column, for P (x) rho and for P^T (sub = 1)
     const uint16_t* psf_order;     // [s*s] footprint offsets by descending PSF weight
     const float4* pc;              // per pixel: (c, 2a, L0, iB), see PixConst
     const float* w;                // raw frame (ADU)
@@ -164,7 +165,6 @@ namespace bdc {
 // ---------------------------------------------------------------------------
 constexpr int NLEV = 12;
 constexpr int LEV_MOMENTS = 10, LEV_FINALIZE = 11;
-constexpr int FT_SIDE = 32;      // output tile side of the forward/proposal kernel
 
 struct TileDesc {
     Frame f;
@@ -188,6 +188,7 @@ enum BatchKind { BK_FORWARD = 0, BK_SERIES = 1, BK_PHASE = 2, BK_MOMENTS = 3, BK
 hipError_t launch_batch_level(int kind, const TileDesc* tiles, const Item* items, int n_items,
                               const double* inv_tab, size_t lds, hipStream_t st);
 hipError_t launch_batch_advance(int64_t* const* tps, int n, hipStream_t st);
-size_t forward_lds(int s);
+size_t forward_lds(int s);                     // of a batch's forward/proposal items
+int forward_items(int h, int w);               // their number for an h x w tile
 
 }  // namespace bdc

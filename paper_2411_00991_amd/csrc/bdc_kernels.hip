@@ -6,6 +6,7 @@
 // batched R-hat statistics, per-chain log-posterior partials) -> finalize
 // (deterministic reduction of the log-posterior, sweep index + 1).
 // The sweep index lives in device memory so a captured sweep replays as is.
+#include "bdc_conv.h"
 #include "bdc_device.h"
 #include "bdc_kernels.h"
 
@@ -203,12 +204,10 @@ __global__ void k_init_state(Frame f, State S, const float* rho0, float log_step
 }
 
 // ---------------------------------------------------------------------------
-// mu = P (x) rho (LDS tile + halo, double accumulation) and this sweep's
+// mu = P (x) rho (bdc_conv.h, double accumulation) and this sweep's
 // proposals: rho' = rho exp(step xi), step = exp(log_step), xi ~ N(0, 1) from
 // stream 0; Hastings + prior terms; log u from stream 1.
 // ---------------------------------------------------------------------------
-constexpr int FT = 32;   // output tile side
-
 // This sweep's proposal for object cell m of one chain (current value r0).
 __device__ inline void propose_cell(const Frame& f, const State& S, const Prior& pr, int64_t m, int chain,
                                     int64_t t, float r0) {
@@ -216,73 +215,31 @@ __device__ inline void propose_cell(const Frame& f, const State& S, const Prior&
     const float xi = box_muller(draw(f.key, (uint32_t)m, (uint32_t)t, (uint32_t)chain, STREAM_PROPOSAL));
     const float step = expf(S.log_step[i]);
     const float hs = step * xi;                 // log rho' - log rho
-    const float rp = r0 * expf(hs);
+    const float e = expf(hs), rp = mul_rn(r0, e);
     float hast = hs;
-    if (pr.kind == 1) hast += (pr.a - 1.0f) * hs - pr.b * (rp - r0);
+    if (pr.kind == 1) hast = fmaf(step, xi, fmaf(pr.a - 1.0f, hs, -(pr.b * fmaf(r0, e, -r0))));
     if (!(rp > 0.0f) || !isfinite(rp)) hast = -INFINITY;
     S.prop[i] = make_float4(rp, hast, logf(u01(draw(f.key, (uint32_t)m, (uint32_t)t, (uint32_t)chain, STREAM_ACCEPT).x)),
-                            rp - r0);
+                            add_rn(rp, -r0));
 }
 
-// One FT x FT output tile of one chain.  lds: (FT + 2r)^2 + s^2 floats.
-__device__ void forward_tile(const Frame& f, const State& S, const Prior& pr, int propose, int tile, int chain,
-                             int64_t t, float* lds) {
-    const int r = f.r, s = f.s, TWd = FT + 2 * r;
-    float* tl = lds;                                                // rho tile with halo, [TWd][TWd]
-    float* sp = lds + TWd * TWd;                                    // PSF, [s][s]
-    const int ntx = (f.W + FT - 1) / FT;
-    const int ty0 = (tile / ntx) * FT, tx0 = (tile % ntx) * FT;
+// One output tile of one chain.
+template <class T>
+__device__ inline void forward_tile(const Frame& f, const State& S, const Prior& pr, int propose, int tile, int chain,
+                                    int64_t t, float* lds) {
     const float* rho = S.rho + (int64_t)chain * f.N;
-    for (int i = threadIdx.x; i < TWd * TWd; i += WG) {
-        const int yy = ty0 - r + i / TWd, xx = tx0 - r + i % TWd;
-        tl[i] = (yy >= 0 && yy < f.H && xx >= 0 && xx < f.W) ? rho[(int64_t)yy * f.W + xx] : 0.0f;
-    }
-    for (int i = threadIdx.x; i < s * s; i += WG) sp[i] = f.psf[i];
-    __syncthreads();
-    // each thread: four adjacent outputs of one tile row; per PSF row the four
-    // share a window of tile values that slides one entry per tap, so each
-    // value is loaded and converted once (every output's FMA order and operands
-    // are those of a tap-by-tap loop)
-    static_assert(FT * FT == 4 * WG, "four outputs per thread");
-    const int ly = threadIdx.x / (FT / 4), lx0 = (threadIdx.x % (FT / 4)) * 4;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int dy = -r; dy <= r; ++dy) {
-        const float* prow = sp + (dy + r) * s + r;                  // prow[dx]
-        const float* trow = tl + (ly - dy + r) * TWd + lx0 + r;     // output k, tap dx: trow[k - dx]
-        double w0 = trow[r], w1 = trow[r + 1], w2 = trow[r + 2], w3 = trow[r + 3];
-        for (int dx = -r; dx < r; ++dx) {
-            const double p = (double)prow[dx];
-            acc[0] = fma(p, w0, acc[0]);
-            acc[1] = fma(p, w1, acc[1]);
-            acc[2] = fma(p, w2, acc[2]);
-            acc[3] = fma(p, w3, acc[3]);
-            w3 = w2;
-            w2 = w1;
-            w1 = w0;
-            w0 = (double)trow[-dx - 1];
-        }
-        const double p = (double)prow[r];
-        acc[0] = fma(p, w0, acc[0]);
-        acc[1] = fma(p, w1, acc[1]);
-        acc[2] = fma(p, w2, acc[2]);
-        acc[3] = fma(p, w3, acc[3]);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int lx = lx0 + k;
-        const int y = ty0 + ly, x = tx0 + lx;
-        if (y >= f.H || x >= f.W) continue;
-        const double accv = acc[k];
-        const int64_t m = (int64_t)y * f.W + x;
-        const int64_t i = (int64_t)chain * f.N + m;
-        S.mu[i] = (float)accv;
-        if (propose) propose_cell(f, S, pr, m, chain, t, rho[m]);
-    }
+    T::run(f.H, f.W, f.r, f.psf64, tile, lds, [&](int y, int x) { return rho[(int64_t)y * f.W + x]; },
+           [&](int y, int x, double sum) {
+               const int64_t m = (int64_t)y * f.W + x;
+               S.mu[(int64_t)chain * f.N + m] = (float)sum;
+               if (propose) propose_cell(f, S, pr, m, chain, t, rho[m]);
+           });
 }
 
+template <class T>
 __global__ void __launch_bounds__(WG) k_forward_propose(Frame f, State S, Prior pr, int propose) {
     extern __shared__ float lds_f[];
-    forward_tile(f, S, pr, propose, blockIdx.x, blockIdx.y, *S.t, lds_f);
+    forward_tile<T>(f, S, pr, propose, blockIdx.x, blockIdx.y, *S.t, lds_f);
 }
 
 // Finer object lattice (sub = k > 1): pixel n's mean, FP64 accumulation over
@@ -1170,21 +1127,25 @@ __device__ inline void series_store_rows(const Frame& f, const State& S, int64_t
         const int gy = ry0 + y, gx = rx0 + xx;
         if (gy >= 0 && gy < f.H && gx >= 0 && gx < f.W) {
             const int ri = (y % f.s) * RW + xx;
-            S.mu[base + (int64_t)gy * f.W + gx] = ring.ma[ri] + ring.A[ri].x;
+            S.mu[base + (int64_t)gy * f.W + gx] = add_rn(ring.ma[ri], ring.A[ri].x);
         }
     }
 }
 
+// D + d of a term, d = d0 w: fused for a thread's first entry.
+__device__ inline float entry_y(bool first, float D, float d0, float w) {
+    return first ? fmaf(w, d0, D) : add_rn(D, mul_rn(d0, w));
+}
+
 // Footprint entry e (in descending PSF weight) of the update at block column lx
 // of block row ly: offset (oy | ox << 8), ring index and the move's change.
-__device__ inline void footprint_entry(const Frame& f, int RW, int ly, int lx, int e, float d0, int& o, int& ri,
-                                       float& dj) {
+__device__ inline void footprint_entry(const Frame& f, int RW, int ly, int lx, int e, int& o, int& ri, float& w) {
     const int s = f.s, j = f.psf_order[e], oy = j / s, ox = j - oy * s;
     int slot = ly % s + oy;
     slot = slot >= s ? slot - s : slot;
     o = oy | ox << 8;
     ri = slot * RW + ox + lx;
-    dj = d0 * f.psf[j];
+    w = f.psf[j];
 }
 
 // This thread's share of Delta with the terms outside their radius evaluated
@@ -1199,16 +1160,17 @@ __device__ inline DirectPart block_direct_part(const Frame& f, const Ring& ring,
 #pragma unroll 1
     for (int e = threadIdx.x; e < F; e += WG) {
         int o, i;
-        float dj;
-        footprint_entry(f, RW, ly, lx, e, d0, o, i, dj);
+        float w;
+        footprint_entry(f, RW, ly, lx, e, o, i, w);
         const float4 A = ring.A[i];
         if (!(A.y >= 0.0f)) continue;
-        if (fabsf(A.x + dj) <= A.y) {
+        const float dj = mul_rn(d0, w), y = entry_y(e < WG, A.x, d0, w);
+        if (fabsf(y) <= A.y) {
             const float2 Bv = ring.B[i];
-            fpart += series_delta(make_float4(A.z, A.w, Bv.x, Bv.y), A.x, dj);
+            fpart = fmaf(dj, series_slope(make_float4(A.z, A.w, Bv.x, Bv.y), A.x, y), fpart);
         } else {
             const PixConst pc = load_pc(f.pc, m + (int64_t)((o & 0xFF) - r) * f.W + ((o >> 8) - r));
-            const float mu = ring.ma[i] + A.x;
+            const float mu = add_rn(ring.ma[i], A.x);
             // a thread's first by the grouped recurrence, further ones term by term
             p.sum += p.n == 0 ? delta_ell_direct(mu, dj, pc, p.terms) : delta_ell_notab(mu, dj, pc, p.terms);
             ++p.n;
@@ -1388,19 +1350,19 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
         auto queue = [&](int q, int i, float mu, float dq, bool first) {
             const int pix = (int)m + ((off[q] & 0xFF) - r) * f.W + ((off[q] >> 8) - r);
             job_pc[i] = make_float4(__int_as_float(pix), -2.0f, 0.0f, 0.0f);
-            job_md[i] = first ? make_float2(mu, dq) : make_float2(mu + dq, 0.0f);
+            job_md[i] = first ? make_float2(mu, dq) : make_float2(add_rn(mu, dq), 0.0f);
             job_ri[i] = ri[q];
         };
 #pragma unroll
         for (int q = 0; q < SER_Q; ++q) {
-            const float dq = d0 * pw[q];
-            y[q] = Aq[q].x + dq;
+            const float dq = mul_rn(d0, pw[q]);
+            y[q] = entry_y(q == 0, Aq[q].x, d0, pw[q]);
             const bool valid = Aq[q].y >= 0.0f;
             fast[q] = fabsf(y[q]) <= Aq[q].y;
             const float4 b = make_float4(Aq[q].z, Aq[q].w, Bq[q].x, Bq[q].y);
             nevals += valid ? 1 : 0;
-            const float sd = series_delta(b, Aq[q].x, dq);
-            if (fast[q]) fpart += sd;
+            const float slope = series_slope(b, Aq[q].x, y[q]);
+            if (fast[q]) fpart = fmaf(dq, slope, fpart);
             const bool need = valid && !fast[q];
             const uint64_t bal = __ballot(need);
             if (bal) {
@@ -1408,14 +1370,14 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
                 if (lane == 0) first = atomicAdd(&s_cnt[cq], __popcll(bal));
                 const float ma = q == 0 ? ma0 : ring.ma[ri[q]];
                 if (need) {
-                    const TermBound tb = series_bound(ma, b, Aq[q].x, y[q], sd);
+                    const TermBound tb = series_bound(ma, b, Aq[q].x, y[q], dq * slope);
                     gpart += tb.c;
                     err += tb.e;
                 }
                 first = __builtin_amdgcn_readfirstlane(first) + lanes_below(bal);
                 if (need) {
                     if (first < cap) {
-                        queue(q, first, ma + Aq[q].x, dq, !any);
+                        queue(q, first, add_rn(ma, Aq[q].x), dq, !any);
                         if (q == 0) job_pc[first] = pcv0;
                     } else left |= any ? 1u << q : 0x100u | 1u << q;
                     any = true;
@@ -1485,7 +1447,7 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
                     float4 rec = job_pc[job0];
                     if (rec.y == -2.0f) rec = f.pc[__float_as_int(rec.x)];
                     const Series nx = series_after(md.x, md.y, pc_of(rec), threadIdx.x & 3, aterms);
-                    if ((threadIdx.x & 3) == 0) anchor(job_ri[job0], nx, md.x + md.y);
+                    if ((threadIdx.x & 3) == 0) anchor(job_ri[job0], nx, add_rn(md.x, md.y));
                 }
                 n0 += cap;
                 if (n <= n0) break;
@@ -1499,7 +1461,7 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
                     if (lane == 0) i = atomicAdd(&s_cnt[3], __popcll(bal));
                     i = __builtin_amdgcn_readfirstlane(i) + lanes_below(bal);
                     if (((left >> q) & 1) && i < cap) {
-                        queue(q, i, ring.ma[ri[q]] + ring.A[ri[q]].x, d0 * pw[q], left & 0x100);
+                        queue(q, i, add_rn(ring.ma[ri[q]], ring.A[ri[q]].x), mul_rn(d0, pw[q]), left & 0x100);
                         left &= ~(0x100u | 1u << q);
                     }
                 }
@@ -1712,12 +1674,12 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int q = g + u;
-                const float dq = d0 * pw[q];
+                const float dq = mul_rn(d0, pw[q]), y = fmaf(pw[q], d0, Aq[u].x);
                 Dq[q] = Aq[u].x;
                 const bool valid = Aq[u].y >= 0.0f;                 // inside the frame (sink: R < 0)
-                const bool in_r = fabsf(Aq[u].x + dq) <= Aq[u].y;
-                const float sd = series_delta(make_float4(Aq[u].z, Aq[u].w, Bq[u].x, Bq[u].y), Aq[u].x, dq);
-                fpart += in_r ? sd : 0.0f;
+                const bool in_r = fabsf(y) <= Aq[u].y;
+                const float sd = mul_rn(dq, series_slope(make_float4(Aq[u].z, Aq[u].w, Bq[u].x, Bq[u].y), Aq[u].x, y));
+                fpart = add_rn(fpart, in_r ? sd : 0.0f);
                 fast |= in_r ? 1u << q : 0u;
                 const bool dir = valid && !in_r;
                 nevals += valid ? 1 : 0;
@@ -1727,7 +1689,7 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
                     const bool queued = dir && slot < QCAP;
                     over |= (dir && !queued) ? 1u << q : 0u;
                     const int ws = queued ? slot : QCAP;
-                    jobs[ws] = make_float4(maq[u] + Aq[u].x, dq, pcq[q].x, pcq[q].y);
+                    jobs[ws] = make_float4(add_rn(maq[u], Aq[u].x), dq, pcq[q].x, pcq[q].y);
                     job_ri[ws] = ring_index(q);
                     nq += __popcll(bal);
                 }
@@ -1748,7 +1710,7 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
             int slot = ly % s + oy;
             slot = slot >= s ? slot - s : slot;
             ri = slot * RW + ox + lx;
-            dq = d0 * f.psf[j];
+            dq = mul_rn(d0, f.psf[j]);
             pix = m + (int64_t)(oy - r) * f.W + (ox - r);
         };
         // 2. Delta from every term's series; too close to call within the bounds
@@ -1815,19 +1777,19 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
             // back unchanged (queued ones are re-anchored just after, in order)
 #pragma unroll
             for (int q = 0; q < NQ; ++q)
-                ring.A[ring_index(q)].x = ((fast >> q) & 1) ? Dq[q] + d0 * pw[q] : Dq[q];
+                ring.A[ring_index(q)].x = ((fast >> q) & 1) ? fmaf(pw[q], d0, Dq[q]) : Dq[q];
             // queued terms left their series' radius: re-anchor at the new mean
 #pragma unroll 1
             for (int j = lane >> 2; j < min(nq, QCAP); j += 16) {
                 const float4 jb = jobs[j];
                 const bool move = j < WS_MOVE;
-                const Series nx = series_after(move ? jb.x : jb.x + jb.y, move ? jb.y : 0.0f, pc_from(jb.z, jb.w),
+                const Series nx = series_after(move ? jb.x : add_rn(jb.x, jb.y), move ? jb.y : 0.0f, pc_from(jb.z, jb.w),
                                                lane & 3, aterms);
                 if ((lane & 3) == 0) {
                     const int i = job_ri[j];
                     ring.A[i] = make_float4(0.0f, nx.R, nx.b.x, nx.b.y);
                     ring.B[i] = make_float2(nx.b.z, nx.b.w);
-                    ring.ma[i] = jb.x + jb.y;
+                    ring.ma[i] = add_rn(jb.x, jb.y);
                     ++nanch;
                 }
             }
@@ -1840,7 +1802,7 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
                         int64_t pix;
                         over_entry(q, ri, dq, pix);
                         if (dq != 0.0f) {
-                            const float mu1 = (ring.ma[ri] + ring.A[ri].x) + dq;
+                            const float mu1 = add_rn(add_rn(ring.ma[ri], ring.A[ri].x), dq);
                             const Series sr = series_at(mu1, load_pc(f.pc, pix), aterms);
                             ring.A[ri] = make_float4(0.0f, sr.R, sr.b.x, sr.b.y);
                             ring.B[ri] = make_float2(sr.b.z, sr.b.w);
@@ -2326,9 +2288,12 @@ hipError_t launch_forward_propose(const Frame& f, const State& S, const Prior& p
         if (propose) hipLaunchKernelGGL(k_propose_sub, dim3(grid1(f.N), f.C), dim3(WG), 0, st, f, S, pr);
         return hipGetLastError();
     }
-    const int nt = ((f.H + FT - 1) / FT) * ((f.W + FT - 1) / FT);
-    hipLaunchKernelGGL(k_forward_propose, dim3(nt, f.C), dim3(WG), forward_lds(f.s), st, f, S, pr, propose);
-    return hipGetLastError();
+    return conv_dispatch(f.N * f.C, [&](auto t) {
+        using T = decltype(t);
+        hipLaunchKernelGGL(k_forward_propose<T>, dim3(T::tiles(f.H, f.W), f.C), dim3(WG), T::lds(f.r), st, f, S, pr,
+                           propose);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_colour_pass(const Frame& f, const State& S, int burn_in, const double* inv_tab, int colour,
@@ -2609,6 +2574,8 @@ hipError_t launch_learned_init(const Frame& f, const State& S, const float* out,
 namespace bdc {
 namespace {
 
+using BatchConv = ConvTile<8, 4>;
+
 __global__ void k_batch_advance(int64_t* const* tps, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) *tps[i] += 1;
@@ -2630,7 +2597,7 @@ k_batch(const TileDesc* tiles, const Item* items, const double* inv_tab) {
     const int64_t t = *T.S.t;
     const int ph = I.level - 1;
     if constexpr (KIND == BK_FORWARD) {
-        forward_tile(T.f, T.S, T.pr, 1, I.index, I.chain, t, (float*)lds_b);
+        forward_tile<BatchConv>(T.f, T.S, T.pr, 1, I.index, I.chain, t, (float*)lds_b);
     } else if constexpr (KIND == BK_SERIES) {
         block_series_block(T.f, T.S, T.burn_in, T.B, ph / 2, ph % 2, I.index, I.chain, t, 0, T.f.s * T.f.s,
                            nullptr, nullptr, lds_b);
@@ -2657,10 +2624,8 @@ __global__ void __launch_bounds__(64) k_batch_wave(const TileDesc* tiles, const 
 
 }  // namespace
 
-size_t forward_lds(int s) {
-    const int TWd = FT + 2 * (s / 2);
-    return (size_t)(TWd * TWd + s * s) * sizeof(float);
-}
+size_t forward_lds(int s) { return BatchConv::lds(s / 2); }
+int forward_items(int h, int w) { return BatchConv::tiles(h, w); }
 
 hipError_t launch_batch_level(int kind, const TileDesc* tiles, const Item* items, int n_items,
                               const double* inv_tab, size_t lds, hipStream_t st) {

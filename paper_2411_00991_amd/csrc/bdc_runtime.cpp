@@ -68,6 +68,7 @@ struct bdc_ctx {
     int max_batches = 0;
 
     float* d_psf = nullptr;
+    double* d_psf64 = nullptr;         // [2][s*s] column by column, see Frame::psf64
     std::vector<double> h_psf;         // normalised PSF (host copy, for the prior's OTF)
     uint16_t* d_psf_order = nullptr;   // footprint offsets by descending PSF weight
     // Dirichlet-OTF prior per chunk (prior_kind DIRICHLET)
@@ -125,7 +126,7 @@ struct bdc_ctx {
         Frame f;
         f.H = cfg.height * sub; f.W = cfg.width * sub; f.s = s; f.r = r; f.N = N; f.C = C;
         f.sub = sub; f.Hp = cfg.height; f.Wp = cfg.width; f.Np = Np;
-        f.psf = d_psf; f.psf_order = d_psf_order; f.pc = d_pc; f.w = d_w; f.gain = d_gain; f.offset = d_off; f.sigma = d_sig;
+        f.psf = d_psf; f.psf64 = d_psf64; f.psf_order = d_psf_order; f.pc = d_pc; f.w = d_w; f.gain = d_gain; f.offset = d_off; f.sigma = d_sig;
         f.cam_per_pixel = cam_per_pixel;
         f.camera = cfg.camera;
         f.key = make_uint2((uint32_t)cfg.seed, (uint32_t)(cfg.seed >> 32));
@@ -183,7 +184,7 @@ struct bdc_ctx {
     void free_all() {
         clear_marks();
         drop_graph();
-        void* ptrs[] = {d_psf, d_psf_order, d_pc, d_w, d_gain, d_off, d_sig, d_inv, d_rho, d_ls, d_mu, d_prop,
+        void* ptrs[] = {d_psf, d_psf64, d_psf_order, d_pc, d_w, d_gain, d_off, d_sig, d_inv, d_rho, d_ls, d_mu, d_prop,
                         d_t, d_acc, d_mean, d_m2, d_batch, d_lp, d_trace, d_bad, d_tmp, d_tmp2,
                         d_tmpd, d_hist, d_dbg_delta, d_dbg_acc, d_ctr, d_pm, d_ps, d_scale, d_bacc,
                         d_bdbg, d_bdbg_acc, d_dir_am1, d_dir_const, d_dir_F, d_dir_part, d_samples, d_probs,
@@ -652,6 +653,15 @@ bdc_status bdc_set_psf(bdc_ctx* c, const float* psf, int32_t ph, int32_t pw, int
         }
         c->d_psf = dalloc<float>(F);
         hipck(hipMemcpy(c->d_psf, nrm.data(), F * sizeof(float), hipMemcpyHostToDevice), "upload PSF");
+        std::vector<double> cols(2 * (size_t)F);
+        for (int x = 0; x < ph; ++x)
+            for (int t = 0; t < ph; ++t) {
+                cols[x * ph + t] = nrm[F - 1 - (t * ph + x)];
+                cols[F + x * ph + t] = nrm[t * ph + x];
+            }
+        if (c->d_psf64) { (void)hipFree(c->d_psf64); c->d_psf64 = nullptr; }
+        c->d_psf64 = dalloc<double>(cols.size());
+        hipck(hipMemcpy(c->d_psf64, cols.data(), cols.size() * sizeof(double), hipMemcpyHostToDevice), "upload PSF");
         // footprint offsets for the block-series pass in descending PSF weight
         // (ties by index): each thread's first entry covers the PSF core, where
         // moves are large, and the heaviest 64 fall on the first wave, so direct
@@ -1822,7 +1832,7 @@ bdc_status bdc_batch_create(bdc_ctx* const* tiles, int32_t n_tiles, void* hip_st
             T.series = c->sched == BDC_SCHED_BLOCK9_SERIES ? 2 : c->sched == BDC_SCHED_BLOCK_SERIES ? 1 : 0;
             const int H = c->cfg.height, W = c->cfg.width, s = c->s, B = c->B, F = s * s;
             const int P = T.series == 2 ? 3 : 2;                // block phases P x P
-            T.count[0] = ((H + FT_SIDE - 1) / FT_SIDE) * ((W + FT_SIDE - 1) / FT_SIDE);
+            T.count[0] = forward_items(H, W);
             const int nby = (H + B - 1) / B, nbx = (W + B - 1) / B;
             for (int ph = 0; ph < P * P; ++ph) {
                 const int py = ph / P, px = ph % P;
@@ -1845,7 +1855,7 @@ bdc_status bdc_batch_create(bdc_ctx* const* tiles, int32_t n_tiles, void* hip_st
             lds_kind[pass_kind] = std::max(lds_kind[pass_kind], pass_lds);
             for (int ch = 0; ch < c->C; ++ch) {
                 for (int k = 0; k < T.count[0]; ++k)
-                    items.push_back({{i, ch, 0, k}, pass_kind, BK_FORWARD, (double)FT_SIDE * FT_SIDE * F});
+                    items.push_back({{i, ch, 0, k}, pass_kind, BK_FORWARD, (double)F});
                 for (int ph = 0; ph < P * P; ++ph) {
                     const int py = ph / P, px = ph % P, nbx_p = (nbx - px + P - 1) / P;
                     for (int k = 0; k < T.count[1 + ph]; ++k) {
