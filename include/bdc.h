@@ -313,9 +313,11 @@ bdc_status bdc_profile(bdc_ctx* ctx, int32_t enable);
  * kernel milliseconds and launches[3] launch counts for the classes
  * (0 forward/proposal, 1 colour or phase passes, 2 moments); work[6] = phi-sum
  * terms of direct footprint evaluations, footprint likelihood evaluations,
- * and for the block-series scans: the footprint terms evaluated directly (few:
- * most decisions follow from bounds), the series anchored (new ring rows,
- * accepted moves out of a radius), the phi-sum terms of those, and 0 (counted
+ * and for the scans that decide from bounds (block-series; block-phase with one
+ * cell per block and colour of an EMCCD frame, the chunk prior or a finer
+ * lattice): the footprint terms evaluated directly (few), the series anchored
+ * (new pixels, accepted moves out of a radius), the phi-sum terms of those (EMCCD:
+ * 0), and 0 (counted
  * on every sweep, profiled or not).  Any pointer may be NULL.  Synchronises. */
 bdc_status bdc_profile_read(bdc_ctx* ctx, double* ms, int64_t* launches, int64_t* work);
 

@@ -288,19 +288,9 @@ constexpr float SERIES_TAU = 3e-9f;
 struct Series { float4 b; float R; };
 __device__ inline float4 no_series() { return make_float4(0.0f, 1.0f, 0.0f, 0.0f); }
 
-// Series of the pixel at mean mu from the window polynomial S(v) =
-// sum_k (W_k / W_ref)(1 + v)^(k - lo) (coefficients S0, A1..A4).
-__device__ inline Series series_finish(double S0, double A1, double A2, double A3, double A4, int lo, float mu) {
+// Series from the coefficients g_j of v^j of the change of log Z.
+__device__ inline Series series_of_log(double g1, double g2, double g3, double g4, float mu) {
     Series out;
-    const double iS = rcp_nr2(S0);
-    const double s1 = A1 * iS, s2 = A2 * iS, s3 = A3 * iS, s4 = A4 * iS;
-    // log(1 + s1 v + s2 v^2 + ...): h_j = s_j - (1/j) sum_{i<j} i h_i s_{j-i}
-    const double h1 = s1;
-    const double h2 = s2 - 0.5 * h1 * s1;
-    const double h3 = s3 - (h1 * s2 + 2.0 * h2 * s1) * (1.0 / 3.0);
-    const double h4 = s4 - 0.25 * (h1 * s3 + 2.0 * h2 * s2 + 3.0 * h3 * s1);
-    const double L = (double)lo;                     // + lo log(1 + v)
-    const double g1 = h1 + L, g2 = h2 - 0.5 * L, g3 = h3 + L * (1.0 / 3.0), g4 = h4 - 0.25 * L;
     const double im = rcp_nr2((double)mu), im2 = im * im;
     out.b = make_float4((float)(g1 * im - 1.0), (float)(g2 * im2), (float)(g3 * im2 * im), (float)(g4 * im2 * im2));
     // radius: u0 = (tau/2 * 5 / s2)^(1/5) solves s2 u^5 / 5 = tau/2; the factor
@@ -311,6 +301,21 @@ __device__ inline Series series_finish(double S0, double A1, double A2, double A
     u *= __builtin_amdgcn_exp2f(0.2f * __builtin_amdgcn_logf(1.0f - u));
     out.R = u * mu;
     return out;
+}
+
+// Series of the pixel at mean mu from the window polynomial S(v) =
+// sum_k (W_k / W_ref)(1 + v)^(k - lo) (coefficients S0, A1..A4).
+__device__ inline Series series_finish(double S0, double A1, double A2, double A3, double A4, int lo, float mu) {
+    const double iS = rcp_nr2(S0);
+    const double s1 = A1 * iS, s2 = A2 * iS, s3 = A3 * iS, s4 = A4 * iS;
+    // log(1 + s1 v + s2 v^2 + ...): h_j = s_j - (1/j) sum_{i<j} i h_i s_{j-i}
+    const double h1 = s1;
+    const double h2 = s2 - 0.5 * h1 * s1;
+    const double h3 = s3 - (h1 * s2 + 2.0 * h2 * s1) * (1.0 / 3.0);
+    const double h4 = s4 - 0.25 * (h1 * s3 + 2.0 * h2 * s2 + 3.0 * h3 * s1);
+    const double L = (double)lo;                     // + lo log(1 + v)
+    const double g1 = h1 + L, g2 = h2 - 0.5 * L, g3 = h3 + L * (1.0 / 3.0), g4 = h4 - 0.25 * L;
+    return series_of_log(g1, g2, g3, g4, mu);
 }
 
 // Sharp read noise (a > A_RECUR_MAX): the few weights of the window relative to

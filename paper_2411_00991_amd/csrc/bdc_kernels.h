@@ -51,9 +51,9 @@ struct State {
     int64_t* t;                    // device copy of the sweep index
     unsigned long long* accepts;   // [C]
     unsigned long long* counters;  // [0] phi terms summed, [1] footprint evaluations,
-                                   // [2] direct evaluations, [3] series anchored (block-series scans:
-                                   // new ring rows, accepted moves out of the radius), [4] their phi
-                                   // terms, [5] unused (0)
+                                   // [2] direct evaluations, [3] series anchored (scans that decide
+                                   // from bounds: new pixels, accepted moves out of the radius),
+                                   // [4] their phi terms, [5] unused (0)
 };
 
 struct Prior { int kind; float a, b; };

@@ -13,6 +13,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace bdc {
 
@@ -475,10 +476,11 @@ __device__ inline void lds_barrier() {
 // and the change of the log prior is
 //   sum_k (alpha_k - 1) log(1 + u_k) / 2  -  (sum_k (alpha_k - 1)) log(S' / S)
 // with S = sum_k |F_k|, S' - S = sum_k d (2 p_k + d) / (|F_k'| + |F_k|): both
-// sums free of cancellation, so FP32 terms keep their relative accuracy.
+// sums free of cancellation, so FP32 terms keep their relative accuracy.  The
+// spectrum is kept in FP64: a move can nearly cancel a component (|F'| << |F|),
+// and log|F'| then needs F' to more digits than FP32 holds.
 // ---------------------------------------------------------------------------
 constexpr int DIR_MAX_B = 32;                 // chunk side (B <= s <= 31 with this prior)
-constexpr int DIR_Q = (DIR_MAX_B * DIR_MAX_B + WG - 1) / WG;
 
 struct ChunkGeom { int y0, x0, th, tw, shape; };
 
@@ -500,25 +502,9 @@ __device__ inline int small_mod(int a, int b, float inv_b) {
     return a - b * q;
 }
 
-// LDS of the chunk prior inside a block pass.  The spectrum is kept in FP64:
-// a move can nearly cancel a component (|F'| << |F|), and log|F'| then needs
-// F' to more digits than FP32 holds.
-struct DirLds {
-    double *re, *im;                          // [K] per frequency, each owned by one thread
-    float* am1;                               // [K] alpha_k - 1
-    double2 *th, *tw;                         // (cos, sin)(2 pi j / n), j < th, j < tw
-    double* red;                              // [2 * WAVES]
-};
-
-__host__ __device__ inline size_t dir_lds_bytes(int B) {
-    return (size_t)2 * B * B * sizeof(double) + (size_t)B * B * sizeof(float) + (size_t)2 * B * sizeof(double2) +
-           2 * WAVES * sizeof(double) + 16;
-}
-
 // One block (index bi among the blocks of phase (py, px)) of one chain.
-// lds: block_phase_lds(B, s) bytes (+ dir_lds_bytes(B) with the chunk prior),
-// 8-byte aligned.
-template <bool DIR, bool EM>
+// lds: block_phase_lds(B, s) bytes, 8-byte aligned.
+template <bool EM>
 __device__ void block_phase_block(const Frame& f, const State& S, int burn_in, const double* inv_tab, int B,
                                   int py, int px, int bi, int chain, int64_t t, int k0, int k1,
                                   float* dbg_delta, uint8_t* dbg_acc, double* lds_d) {
@@ -532,17 +518,6 @@ __device__ void block_phase_block(const Frame& f, const State& S, int burn_in, c
     uint8_t* s_cls = (uint8_t*)(s_off + F);                  // [RW*RW] window class
     __shared__ float s_d[MAX_ACT];                           // rho' - rho of the colour's pixels
     __shared__ WaveSort s_ws[WAVES];
-    DirLds dl;
-    if (DIR) {
-        uintptr_t a = reinterpret_cast<uintptr_t>(s_cls + RW * RW);
-        a = (a + 15) & ~(uintptr_t)15;
-        dl.red = reinterpret_cast<double*>(a);
-        dl.th = reinterpret_cast<double2*>(dl.red + 2 * WAVES);
-        dl.tw = dl.th + B;
-        dl.re = reinterpret_cast<double*>(dl.tw + B);
-        dl.im = dl.re + B * B;
-        dl.am1 = reinterpret_cast<float*>(dl.im + B * B);
-    }
 
     const int nbx = (f.W + B - 1) / B;
     const int nbx_p = (nbx - px + 1) / 2;
@@ -566,52 +541,10 @@ __device__ void block_phase_block(const Frame& f, const State& S, int burn_in, c
         if (sorted)
             s_cls[i] = in ? (uint8_t)window_class(__builtin_amdgcn_sqrtf(2.0f * TAIL_T / f.pc[n].y)) : 0;
     }
-    // chunk prior: this block's spectrum (computed from rho before the pass),
-    // per-frequency data owned by thread j % WG, the modulus sum S, twiddles
-    double dS_tot = 0.0;
-    int dK = 0;
-    float inv_bh = 0.0f, inv_bw = 0.0f;
-    int jy[DIR_Q], jx[DIR_Q];
-    if (DIR) {
-        dK = bh * bw;
-        inv_bh = 1.0f / (float)bh;
-        inv_bw = 1.0f / (float)bw;
-        const int shape = (bh < B ? 2 : 0) + (bw < B ? 1 : 0);
-        const float* am = f.dir_am1 + (size_t)shape * B * B;
-        double sab = 0.0;
-#pragma unroll
-        for (int q = 0; q < DIR_Q; ++q) {
-            const int j = threadIdx.x + q * WG;
-            jy[q] = j < dK ? j / bw : 0;
-            jx[q] = j < dK ? j - (j / bw) * bw : 0;
-            if (j < dK) {
-                const double2 F = f.dir_F[base + (int64_t)(by0 + jy[q]) * f.W + (bx0 + jx[q])];
-                dl.re[j] = F.x;
-                dl.im[j] = F.y;
-                dl.am1[j] = am[j];
-                sab += sqrt(F.x * F.x + F.y * F.y);
-            }
-        }
-        for (int j = threadIdx.x; j < bh; j += WG) {
-            double sn, cs;
-            sincospi(2.0 * j / bh, &sn, &cs);
-            dl.th[j] = make_double2(cs, sn);
-        }
-        for (int j = threadIdx.x; j < bw; j += WG) {
-            double sn, cs;
-            sincospi(2.0 * j / bw, &sn, &cs);
-            dl.tw[j] = make_double2(cs, sn);
-        }
-        sab = wave_sum(sab);
-        if ((threadIdx.x & 63) == 0) dl.red[threadIdx.x >> 6] = sab;
-        __syncthreads();
-        for (int w = 0; w < WAVES; ++w) dS_tot += dl.red[w];
-    }
     __syncthreads();
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     WaveSort& ws = s_ws[wave];
     int nterms = 0, nevals = 0;
-    double dwr[DIR_Q], dwi[DIR_Q];                             // this update's twiddles (chunk prior)
 
     for (int k = k0; k < k1; ++k) {
         const int ky = k / s, kx = k - (k / s) * s;
@@ -672,39 +605,6 @@ __device__ void block_phase_block(const Frame& f, const State& S, int burn_in, c
             }
             part = wave_sum(part);
             if (lane == 0) s_red[wave] = part;
-            if (DIR) {
-                double tsum = 0.0, dsum = 0.0;
-#pragma unroll
-                for (int q = 0; q < DIR_Q; ++q) {
-                    const int j = threadIdx.x + q * WG;
-                    dwr[q] = 0.0;
-                    dwi[q] = 0.0;
-                    if (j < dK) {
-                        const double2 cy = dl.th[small_mod(jy[q] * ly, bh, inv_bh)];
-                        const double2 cx = dl.tw[small_mod(jx[q] * lx, bw, inv_bw)];
-                        const double wr = cy.x * cx.x - cy.y * cx.y;
-                        const double wi = -(cy.y * cx.x + cy.x * cx.y);
-                        dwr[q] = wr;
-                        dwi[q] = wi;
-                        const double re = dl.re[j], im = dl.im[j], dd = (double)d;
-                        const double n2 = re * re + im * im;
-                        const double re1 = fma(dd, wr, re), im1 = fma(dd, wi, im);
-                        const double n21 = re1 * re1 + im1 * im1;
-                        // |F'|^2 - |F|^2 without cancellation for small moves;
-                        // the ratio itself when the component shrinks a lot
-                        const double num = dd * (2.0 * (re * wr + im * wi) + dd);
-                        const float lr = num > -0.5 * n2 ? log1p_k((float)(num / n2)) : fast_ln((float)(n21 / n2));
-                        tsum += (double)(dl.am1[j] * 0.5f * lr);
-                        dsum += num / (double)(__builtin_amdgcn_sqrtf((float)n21) + __builtin_amdgcn_sqrtf((float)n2));
-                    }
-                }
-                tsum = wave_sum(tsum);
-                dsum = wave_sum(dsum);
-                if (lane == 0) {
-                    dl.red[wave] = tsum;
-                    dl.red[WAVES + wave] = dsum;
-                }
-            }
         } else {
             for (int a = 0; a < nact; ++a) {
                 const int ly = ky + s * (a / nax), lx = kx + s * (a % nax);
@@ -731,16 +631,6 @@ __device__ void block_phase_block(const Frame& f, const State& S, int burn_in, c
             const int64_t m = (int64_t)(by0 + ly) * f.W + (bx0 + lx);
             double tot = 0.0;
             for (int w = 0; w < WG / 64; ++w) tot += s_red[a * (WG / 64) + w];
-            double dS = 0.0;
-            if (DIR) {
-                double tp = 0.0;
-                for (int w = 0; w < WAVES; ++w) {
-                    tp += dl.red[w];
-                    dS += dl.red[WAVES + w];
-                }
-                // - sum_k (alpha_k - 1) log(S' / S) with sum_k (alpha_k - 1) = 1 - K
-                tot += tp + (double)(dK - 1) * log1p(dS / dS_tot);
-            }
             const float d = s_d[a];
             const bool acc = (nact == 1 && sorted)
                 ? decide_commit(f, S, chain, m, t, burn_in, tot, threadIdx.x == 0, pre_hast, pre_logu, pre_rp,
@@ -754,17 +644,6 @@ __device__ void block_phase_block(const Frame& f, const State& S, int burn_in, c
                     const float muv = s_mu[ri];
                     if (muv < 0.0f) continue;
                     s_mu[ri] = muv + d * s_psf[j];
-                }
-                if (DIR) {
-#pragma unroll
-                    for (int q = 0; q < DIR_Q; ++q) {
-                        const int j = threadIdx.x + q * WG;
-                        if (j < dK) {
-                            dl.re[j] = fma((double)d, dwr[q], dl.re[j]);
-                            dl.im[j] = fma((double)d, dwi[q], dl.im[j]);
-                        }
-                    }
-                    dS_tot += dS;
                 }
             }
         }
@@ -784,7 +663,7 @@ __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(5))) k_
     extern __shared__ double lds_d[];
     int bi, chain;
     if (!xcd_block(nblk, f.C, bi, chain)) return;
-    block_phase_block<false, EM>(f, S, burn_in, inv_tab, B, py, px, bi, chain, *S.t, k0, k1, dbg_delta, dbg_acc,
+    block_phase_block<EM>(f, S, burn_in, inv_tab, B, py, px, bi, chain, *S.t, k0, k1, dbg_delta, dbg_acc,
                                  lds_d);
 }
 
@@ -881,18 +760,6 @@ __global__ void __launch_bounds__(WG) k_block_phase_sub(Frame f, State S, int bu
         if (yy >= 0 && yy < f.Hp && xx >= 0 && xx < f.Wp) S.mu[pbase + (int64_t)yy * f.Wp + xx] = s_mu[i];
     }
     count_work(S.counters, nterms, nevals);
-}
-
-// The block-phase pass with the Dirichlet-OTF prior per chunk (B <= s <= 31).
-template <bool EM>
-__global__ void __launch_bounds__(WG) k_block_phase_dir(Frame f, State S, int burn_in, const double* inv_tab,
-                                                        int B, int py, int px, int k0, int k1,
-                                                        float* dbg_delta, uint8_t* dbg_acc, int nblk) {
-    extern __shared__ double lds_d[];
-    int bi, chain;
-    if (!xcd_block(nblk, f.C, bi, chain)) return;
-    block_phase_block<true, EM>(f, S, burn_in, inv_tab, B, py, px, bi, chain, *S.t, k0, k1, dbg_delta, dbg_acc,
-                                lds_d);
 }
 
 // Every chunk's spectrum (MODE 0: into f.dir_F) or log prior (MODE 1: into
@@ -1833,6 +1700,553 @@ __global__ void __launch_bounds__(64) k_wave_series(Frame f, State S, int burn_i
 }
 
 // ---------------------------------------------------------------------------
+// Block-phase pass decided by bounds: the direct scan of the EMCCD reading, of
+// the chunk prior and of a finer object lattice, for blocks with one active
+// cell per colour (B <= s).  LDS holds, beside the region's means, a local
+// series of every region pixel, which serves to bound Delta only: when log u
+// lies outside the bound the decision is known; else (and when Delta itself is
+// asked for) every footprint term is evaluated directly, as in k_block_phase.
+// Means, states and decisions are those of the all-direct pass.
+//
+// The series need not give a value, so its anchor may stay behind, up to BND_R
+// radii and half the mean away; the truncation there, for each of a term's two
+// points at most (p_4 / 5) |v|^5 / (1 - |v|) (p_4, v as at series_bound; |v| <= 1/2),
+// is charged term by term.  Beyond, series_bound gives the term's interval, and
+// an accepted move re-anchors the pixel.
+//
+// EMCCD pixels: the reading's factor is A + B f(mu), f = sqrt(mu / c) I_1(2
+// sqrt(mu c)), whose zeros in mu are real and not positive, so that log f is a
+// sum of log(1 + beta v) and has the bounds of the sCMOS log-likelihood.  With
+// w = B f / (A + B f) at the anchor and g the change of log f from there, that
+// of log(A + B f) is log(1 + w (e^g - 1)), whose slope in g lies in [0, 1].
+//
+// Chunk prior: F_-k = conj F_k for a real object, so a thread holds one frequency
+// of each such pair, its sums in FP32 with their rounding in the bound; the
+// modulus sum's FP64 change is formed when a move is accepted.
+//
+// What bounds it: the chain of one block's updates (reduce, decide, commit), one
+// workgroup per CU where the region takes the LDS (28 bytes a pixel: 104 KB at
+// 31 x 31), so a workgroup has eight wavefronts there, and an update touches no
+// global memory: a row's proposals are loaded a row ahead, one per lane, and its
+// outcomes stored at its end.  Measured, two sweeps of two chains against the
+// all-direct pass: EMCCD 384 x 500, PSF 21 x 21: 54.5 -> 5.0 ms (1.4 us per update
+// of a block; four wavefronts of two terms a lane: 5.8 ms); chunk prior 512^2, 31 x 31:
+// 68.5 -> 12.9 ms; 512^2 at k = 2, PSF 63 x 63: 285 -> 58 ms.
+// ---------------------------------------------------------------------------
+constexpr float BND_R = 6.0f;
+constexpr float BND_FLAT = 1e-7f;             // of a term: the direct evaluation's absolute rounding
+constexpr size_t BND_LDS_MAX = 160 * 1024;
+constexpr int BND_MAX_F = 3 * 512;            // footprint entries (three per thread of eight waves)
+
+// Series of log f and the share w of B f of an EMCCD pixel at mean mu.
+struct EmSeries { Series s; float w; };
+
+__device__ __noinline__ EmSeries emccd_series(float muf, float cf, float lA, float lB) {
+    EmSeries o;
+    o.s.R = 0.0f;
+    o.s.b = no_series();
+    o.w = 1.0f;
+    if (!(muf > 0.0f)) return o;
+    if (!(cf > 0.0f)) {                                             // no photon amplified: exactly -mu
+        o.s.b = make_float4(-1.0f, 0.0f, 0.0f, 0.0f);
+        o.s.R = muf;
+        return o;
+    }
+    const double mu = (double)muf, c = (double)cf, q = mu * c, z = 2.0 * sqrt(q);
+    double lf;
+    if (z < 16.0) {
+        // t_k = q^k / (k! (k + 1)!):  sum t_k = 2 I_1 / z, sum (k + 1) t_k = I_0;
+        // mu f' / f = their ratio E, mu^2 f'' = q f
+        double t = 1.0, s0 = 1.0, s1 = 1.0;
+#pragma unroll 4
+        for (int k = 1; k < 64; ++k) {
+            t *= q * rcp_nr((double)(k * (k + 1)));
+            s1 += t;
+            s0 = fma((double)(k + 1), t, s0);
+            if (t < 1e-13 * s1) break;
+        }
+        const double E = s0 * rcp_nr2(s1);
+        lf = (double)fast_ln((float)(mu * s1));
+        o.s = series_finish(1.0, E, 0.5 * q, q * (E - 1.0) * (1.0 / 6.0), q * (q - 2.0 * E + 2.0) * (1.0 / 24.0), 0,
+                            muf);
+    } else {
+        // log f = log(mu / c) / 2 + z - log(2 pi z) / 2 + l(z), z ~ (1 + v)^(1/2) and
+        // l = -3/8 / z - 3/16 / z^2 - 21/128 / z^3 - 0.2109 / z^4 (Hankel's series)
+        const float zf = (float)z, i1 = fast_rcp(zf), l1 = -0.375f * i1, l2 = -0.1875f * i1 * i1,
+                    l3 = -0.1640625f * i1 * i1 * i1, l4 = -0.2109f * i1 * i1 * i1 * i1;
+        const float g1 = 0.5f * zf + 0.25f - 0.5f * l1 - l2 - 1.5f * l3 - 2.0f * l4;
+        const float g2 = -0.125f * zf - 0.125f + 0.375f * l1 + l2 + 1.875f * l3 + 3.0f * l4;
+        const float g3 = 0.0625f * zf + 0.083333333f - 0.3125f * l1 - l2 - 2.1875f * l3 - 4.0f * l4;
+        const float g4 = -0.0390625f * zf - 0.0625f + 0.2734375f * l1 + l2 + 2.4609375f * l3 + 5.0f * l4;
+        lf = (double)(0.5f * (fast_ln(muf * fast_rcp(cf)) - fast_ln(6.2831853f * zf)) + (l1 + l2 + l3 + l4)) + z;
+        o.s = series_of_log(g1, g2, g3, g4, muf);
+    }
+    const float lam = (float)((double)lB + lf - (double)lA);         // log(B f / A)
+    if (lam < 30.0f) o.w = fast_rcp(1.0f + __builtin_amdgcn_exp2f(-1.44269504f * lam));
+    if (!(o.s.b.y <= 0.0f)) {
+        o.s.b = no_series();
+        o.s.R = 0.0f;
+    }
+    return o;
+}
+
+// log(1 + w (e^g - 1)), 0 <= w <= 1, and the argument of the logarithm.
+__device__ inline float em_mix(float w, float g, float& arg) {
+    arg = fmaf(w, __builtin_amdgcn_exp2f(g * 1.44269504f) - 1.0f, 1.0f);
+    return fast_ln(arg);
+}
+
+struct BoundedLds {
+    double *red, *red2;                          // [waves]: direct sums; the prior's exact S' - S
+    float4* bnd;                                 // [2][waves]: centre, half-width, S' - S
+    int* cnt;                                    // [4]: queued pixels of three updates in turn
+    float4* A;                                   // [RW * RW + 1]: anchor mean, reach of its series, b1, b2
+    float2* B;                                   // b3, b4
+    float* mu;                                   // current mean, -1 outside the frame
+    float* w;                                    // EMCCD: share of B f
+    uint16_t* job;                               // [F]: queued pixels, region index
+    float* job_mu;                               // [F]: their means after the move
+    double2 *th, *tw;                            // chunk prior: (cos, sin)(2 pi j / n), j < th, j < tw
+};
+
+__host__ __device__ inline size_t bounded_layout(int B, int s, bool em, bool dir, char* base, BoundedLds* out) {
+    const int RW = B + 2 * (s / 2), NR = RW * RW + 1, F = s * s, NW = 8;
+    size_t at = 0;
+    BoundedLds l;
+    auto take = [&](size_t n) {
+        char* p = base + at;
+        at += (n + 15) / 16 * 16;
+        return p;
+    };
+    l.red = (double*)take(NW * sizeof(double));
+    l.red2 = (double*)take(NW * sizeof(double));
+    l.bnd = (float4*)take(2 * NW * sizeof(float4));
+    l.cnt = (int*)take(4 * sizeof(int));
+    l.A = (float4*)take(NR * sizeof(float4));
+    l.B = (float2*)take(NR * sizeof(float2));
+    l.mu = (float*)take(NR * sizeof(float));
+    l.w = (float*)take(em ? NR * sizeof(float) : 0);
+    l.job = (uint16_t*)take(F * sizeof(uint16_t));
+    l.job_mu = (float*)take(F * sizeof(float));
+    l.th = (double2*)take(dir ? B * sizeof(double2) : 0);
+    l.tw = (double2*)take(dir ? B * sizeof(double2) : 0);
+    if (out) *out = l;
+    return at;
+}
+
+// A thread's frequency of the chunk prior (and its conjugate's, weight n = 2).
+struct DirFreq {
+    double re, im;                               // spectrum
+    float amA, amB;                              // alpha - 1 of the two (amB = 0 where they are one)
+    float n;                                     // 0: no frequency
+    int jy, jx;
+};
+
+// Exact change of the log prior under d at the cell of row ly, column lx, but
+// for the modulus sum's logarithm: terms tsum, S' - S dsum; w the twiddle.
+struct DirDelta { double tsum, dsum, wr, wi; };
+
+__device__ inline DirDelta dir_delta(const DirFreq& z, double2 cy, double2 cx, float d0) {
+    DirDelta o;
+    const double wr = cy.x * cx.x - cy.y * cx.y, wi = -(cy.y * cx.x + cy.x * cx.y);
+    const double re = z.re, im = z.im, dd = (double)d0;
+    const double n2 = re * re + im * im;
+    const double re1 = fma(dd, wr, re), im1 = fma(dd, wi, im);
+    const double n21 = re1 * re1 + im1 * im1;
+    // |F'|^2 - |F|^2 without cancellation for small moves; the ratio itself when
+    // the component shrinks a lot
+    const double num = dd * (2.0 * (re * wr + im * wi) + dd);
+    const float lr = num > -0.5 * n2 ? log1p_k((float)(num / n2)) : fast_ln((float)(n21 / n2));
+    o.tsum = (double)(z.amA * 0.5f * lr) + (double)(z.amB * 0.5f * lr);
+    o.dsum = (double)z.n * (num / (double)(__builtin_amdgcn_sqrtf((float)n21) + __builtin_amdgcn_sqrtf((float)n2)));
+    o.wr = wr;
+    o.wi = wi;
+    return o;
+}
+
+// One block (index bi among the blocks of phase (py, px)) of one chain: NT
+// threads, NQ footprint entries each (NT NQ >= F).
+template <bool EM, bool DIR, bool SUB, int NT, int NQ>
+__device__ void bounded_block(const Frame& f, const State& S, int burn_in, const double* inv_tab, int B, int py,
+                              int px, int bi, int chain, int64_t t, int k0, int k1, float* dbg_delta,
+                              uint8_t* dbg_acc, char* lds) {
+    constexpr int NW = NT / 64;
+    const int s = f.s, r = f.r, F = s * s, k = SUB ? f.sub : 1;
+    const int RW = B + 2 * r, NR = RW * RW;
+    BoundedLds l;
+    bounded_layout(B, s, EM, DIR, lds, &l);
+    const int nbx = (f.Wp + B - 1) / B;
+    const int nbx_p = (nbx - px + 1) / 2;
+    const int by = py + 2 * (bi / nbx_p), bx = px + 2 * (bi % nbx_p);
+    const int by0 = by * B, bx0 = bx * B;
+    const int bh = min(B, f.Hp - by0), bw = min(B, f.Wp - bx0);
+    const int64_t base = (int64_t)chain * f.N, pbase = (int64_t)chain * f.Np;
+    const int ry0 = by0 - r, rx0 = bx0 - r;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
+    const bool want_delta = dbg_delta || dbg_acc;
+    int nterms = 0, nevals = 0, ndirect = 0, nanch = 0, aterms = 0;
+
+    // this thread's footprint entries: region offset (padding: none), weight
+    int off[NQ];
+    float pw[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int e = threadIdx.x + q * NT;
+        off[q] = e < F ? (e / s) * RW + e % s : -1;
+        pw[q] = e < F && !SUB ? f.psf[e] : 0.0f;
+    }
+    auto region_pc = [&](int i) {
+        const int y = i / RW;
+        return load_pc(f.pc, (int64_t)(ry0 + y) * f.Wp + (rx0 + i - y * RW));
+    };
+    auto set_series = [&](int i, float m, const Series& sr) {
+        // (counts so large that the direct window may be refused: left to series_bound)
+        const float reach = m * (fabsf(sr.b.x) + 1.0f) < 1e5f ? fminf(BND_R * sr.R, 0.5f * m) : 0.0f;
+        l.A[i] = make_float4(m, reach, sr.b.x, sr.b.y);
+        l.B[i] = make_float2(sr.b.z, sr.b.w);
+        ++nanch;
+    };
+    auto anchor_em = [&](int i, float m) {
+        const PixConst pc = region_pc(i);
+        const EmSeries es = emccd_series(m, pc.c, pc.L0, pc.iB);
+        set_series(i, m, es.s);
+        l.w[i] = es.w;
+    };
+    for (int i = threadIdx.x; i <= NR; i += NT) {
+        const int y = i / RW, yy = ry0 + y, xx = rx0 + i - y * RW;
+        float mu = -1.0f;
+        l.A[i] = make_float4(0.0f, -1.0f, 0.0f, 0.0f);
+        l.B[i] = make_float2(0.0f, 0.0f);
+        if (EM) l.w[i] = 1.0f;
+        if (i < NR && yy >= 0 && yy < f.Hp && xx >= 0 && xx < f.Wp) {
+            mu = S.mu[pbase + (int64_t)yy * f.Wp + xx];
+            if (!want_delta) {
+                if constexpr (EM) anchor_em(i, mu);
+                else set_series(i, mu, series_at(mu, region_pc(i), aterms));
+            }
+        }
+        l.mu[i] = mu;
+    }
+    if (threadIdx.x < 4) l.cnt[threadIdx.x] = 0;
+    // chunk prior: the block's spectrum (computed from rho before the pass), one
+    // frequency of each conjugate pair per thread (rows 0 .. th / 2, of rows 0 and
+    // th / 2 the columns 0 .. tw / 2), the modulus sum S, twiddles
+    double dS_tot = 0.0;
+    const int dK = bh * bw;
+    const float inv_bh = 1.0f / (float)bh, inv_bw = 1.0f / (float)bw;
+    DirFreq fr = {1.0, 0.0, 0.0f, 0.0f, 0.0f, 0, 0};
+    float fre = 1.0f, fim = 0.0f, fabs_F = 1.0f, finv = 1.0f;        // FP32: spectrum, modulus, 1 / modulus
+    auto dir_round = [&]() {
+        fre = (float)fr.re;
+        fim = (float)fr.im;
+        const float n2 = (float)(fr.re * fr.re + fr.im * fr.im);
+        fabs_F = __builtin_amdgcn_sqrtf(n2);
+        finv = fast_rcp(fabs_F);
+    };
+    if (DIR) {
+        const int shape = (bh < B ? 2 : 0) + (bw < B ? 1 : 0);
+        const float* am = f.dir_am1 + (size_t)shape * B * B;
+        const int half = bw / 2 + 1, e = threadIdx.x, mid = half + (bh - 1) / 2 * bw;
+        const int jy = e < half ? 0 : e < mid ? 1 + (e - half) / bw : bh / 2;
+        const int jx = e < half ? e : e < mid ? (e - half) % bw : e - mid;
+        if (e < mid || ((bh & 1) == 0 && e < mid + half)) {
+            const int cy = jy ? bh - jy : 0, cx = jx ? bw - jx : 0;  // the conjugate's
+            const bool self = cy == jy && cx == jx;
+            const double2 Fk = f.dir_F[base + (int64_t)(by0 + jy) * f.W + (bx0 + jx)];
+            fr = {Fk.x, Fk.y, am[jy * bw + jx], self ? 0.0f : am[cy * bw + cx], self ? 1.0f : 2.0f, jy, jx};
+            dS_tot = (double)fr.n * sqrt(Fk.x * Fk.x + Fk.y * Fk.y);
+            dir_round();
+        }
+        for (int j = threadIdx.x; j < bh; j += NT) {
+            double sn, cs;
+            sincospi(2.0 * j / bh, &sn, &cs);
+            l.th[j] = make_double2(cs, sn);
+        }
+        for (int j = threadIdx.x; j < bw; j += NT) {
+            double sn, cs;
+            sincospi(2.0 * j / bw, &sn, &cs);
+            l.tw[j] = make_double2(cs, sn);
+        }
+        dS_tot = wave_sum(dS_tot);
+        if (lane == 0) l.red2[wave] = dS_tot;
+        __syncthreads();
+        dS_tot = 0.0;
+        for (int w = 0; w < NW; ++w) dS_tot += l.red2[w];
+    }
+    __syncthreads();
+
+    const float gain = t < burn_in ? exp2f(-0.6f * log2f((float)t + 1.0f)) : 0.0f;
+    const float flat = BND_FLAT * (float)F;
+    // the visited colours, cell phase major: phase, block row, column
+    auto settle = [&](int& p, int& y, int& x) {                     // from (p, y, x) to the next one with a cell here
+        while ((p * s + y) * s + x < k1) {
+            if (y >= bh) {
+                ++p;
+                y = 0;
+                x = 0;
+            } else if (x >= bw) {
+                ++y;
+                x = 0;
+            } else {
+                return true;
+            }
+        }
+        return false;
+    };
+    auto cell = [&](int p, int y, int x) {
+        return SUB ? base + (int64_t)((by0 + y) * k + p / k) * f.W + ((bx0 + x) * k + p % k)
+                   : base + (int64_t)(by0 + y) * f.W + (bx0 + x);
+    };
+    float4 n_pr = make_float4(0.0f, 0.0f, 0.0f, 0.0f);              // the next row's inputs, column x in lane x
+    float n_ls = 0.0f;
+    auto prefetch = [&](int p, int y) {
+        if (lane >= bw) return;
+        const int64_t i = cell(p, y, lane);
+        n_pr = S.prop[i];
+        if (t < burn_in) n_ls = S.log_step[i];
+    };
+    int ph = k0 / F, ly = (k0 - ph * F) / s, lx0 = k0 % s, ph_w = -1;
+    bool more = settle(ph, ly, lx0);
+    if (more) prefetch(ph, ly);
+    unsigned n_acc = 0;
+    int par = 0, cq = 0;
+    while (more) {
+        const float4 pr = n_pr;
+        const float ls = n_ls;
+        int nph = ph, nly = ly, nlx = s;
+        more = settle(nph, nly, nlx);
+        if (more) prefetch(nph, nly);
+        if (SUB && ph != ph_w) {
+            ph_w = ph;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) pw[q] = off[q] >= 0 ? f.psf[ph * F + threadIdx.x + q * NT] : 0.0f;
+        }
+        const int lx1 = min(bw, k1 - (ph * s + ly) * s);
+        bool my_acc = false;
+        const double2 cy = DIR ? l.th[small_mod(fr.jy * ly, bh, inv_bh)] : make_double2(0.0, 0.0);
+        const float cyr = (float)cy.x, cyi = (float)cy.y;
+#pragma unroll 1
+        for (int lx = lx0; lx < lx1; ++lx) {
+            const float hast = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pr.y), lx));
+            const float logu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pr.z), lx));
+            const float d0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pr.w), lx));
+            const int origin = ly * RW + lx;
+            // 1. centre and half-width of every term; pixels that an accepted move
+            // takes out of their series' reach are queued
+            float mq[NQ], cen = 0.0f, err = 0.0f, dsum = 0.0f;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                mq[q] = -1.0f;
+                if (q > 1 && wave0 + q * NT >= F) continue;         // none of this wave's entries
+                const int i = off[q] >= 0 ? origin + off[q] : NR;
+                mq[q] = l.mu[i];
+                const float4 A = l.A[i];
+                const float2 Bv = l.B[i];
+                const float share = EM ? l.w[i] : 1.0f;
+                const float4 b = make_float4(A.z, A.w, Bv.x, Bv.y);
+                const bool valid = mq[q] >= 0.0f;
+                nevals += valid ? 1 : 0;
+                const float d = mul_rn(d0, pw[q]), D = mq[q] - A.x, y = D + d;
+                const float cnt = fabsf(b.x) + 1.0f;
+                const bool out = valid && !want_delta && !(fabsf(y) <= A.y);
+                const float ym = out ? fabsf(D) : fmaxf(fabsf(y), fabsf(D)), y2 = ym * ym;
+                const float trunc = fabsf(b.w) * (y2 * y2) * (3.2f * ym * fast_rcp(A.x));
+                float c = d * series_slope(b, D, y), e = 4e-6f * cnt * fabsf(d);
+                if (out) {
+                    const TermBound tb = series_bound(A.x, b, D, y, c);
+                    c = tb.c;
+                    e = tb.e;
+                }
+                if (EM) {
+                    const float gD = fmaf(D, series_slope(b, 0.0f, D), D), gy = gD + c + d;
+                    if (share < 1.0f) {
+                        float ay, aD;
+                        const float my = em_mix(share, gy, ay), mD = em_mix(share, gD, aD);
+                        c = my - mD - d;
+                        // rounding of the share, exponentials, arguments and logarithms
+                        e += fmaf(5e-7f, fabsf(gy) + fabsf(gD), 5e-6f) + 5e-7f * fast_rcp(fminf(ay, aD)) +
+                             4e-6f * cnt * fabsf(D);
+                        if (!(gy < 60.0f && ay > 0.0f && aD > 0.0f)) e = INFINITY;
+                    } else if (!(gy > -12.0f) && b.x != -1.0f) {
+                        e = INFINITY;                               // A, left out, might count
+                    }
+                }
+                // (and the rounding of the sums of centres)
+                if (valid) {
+                    const bool known = e + trunc < INFINITY;
+                    cen += known ? c : 0.0f;
+                    err += known ? fmaf(1.3e-6f, fabsf(c), e + trunc) : INFINITY;
+                }
+                const uint64_t bal = __ballot(out);
+                if (bal) {
+                    int slot = 0;
+                    if (lane == 0) slot = atomicAdd(&l.cnt[cq], __popcll(bal));
+                    slot = __builtin_amdgcn_readfirstlane(slot) + lanes_below(bal);
+                    if (out) {
+                        l.job[slot] = (uint16_t)i;
+                        l.job_mu[slot] = fmaf(d0, pw[q], mq[q]);
+                    }
+                }
+            }
+            const int cq1 = cq == 2 ? 0 : cq + 1;
+            if (threadIdx.x == 0) l.cnt[cq1] = 0;                   // read last before the previous update's barrier
+            // 2. the chunk prior: with h = d / |F| and x = F conj(w) / |F|, u = h (2 Re x + h)
+            // to 5e-7 h (2 + h); its logarithm and |F'| - |F| = |F| u / (1 + sqrt(1 + u))
+            double2 cx = make_double2(0.0, 0.0);
+            if (DIR) {
+                cx = l.tw[small_mod(fr.jx * lx, bw, inv_bw)];
+                const float cxr = (float)cx.x, cxi = (float)cx.y;
+                const float wr = cyr * cxr - cyi * cxi, wi = -(cyi * cxr + cyr * cxi);
+                const float h = d0 * finv, u = h * fmaf(2.0f, (fre * wr + fim * wi) * finv, h), u1 = 1.0f + u;
+                const float du = 1e-6f * fabsf(h) * (2.0f + fabsf(h)) + 1e-7f;
+                const float am = 0.5f * (fr.amA + fr.amB), rt = __builtin_amdgcn_sqrtf(u1), ir = fast_rcp(u1);
+                const float lr = fast_ln(u1), ds = fr.n * fabs_F * u * fast_rcp(1.0f + rt);
+                const float scale = (float)(dK - 1) * fast_rcp((float)dS_tot);
+                float e = 1.5f * fabsf(am) * fmaf(du, ir, 5e-7f * fabsf(lr)) +
+                          scale * fmaf(2e-6f, fabsf(ds), fr.n * fabs_F * du * rt * ir);
+                if (!(du < 0.2f * u1)) e = INFINITY;
+                if (fr.n > 0.0f) {
+                    const bool known = e < INFINITY;
+                    cen += known ? am * lr : 0.0f;
+                    dsum = known ? ds : 0.0f;
+                    err += known ? fmaf(1.3e-6f, fabsf(am * lr), e) : INFINITY;
+                }
+                dsum = wave_sum_dpp_f(dsum);
+            }
+            // 3. sums
+            cen = wave_sum_dpp_f(cen);
+            err = wave_sum_dpp_f(err);
+            if (lane == 0) l.bnd[par * NW + wave] = make_float4(cen, err, dsum, 0.0f);
+            lds_barrier();
+            float tot_c = 0.0f, tot_e = want_delta ? INFINITY : flat, tot_s = 0.0f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const float4 v = l.bnd[par * NW + w];
+                tot_c += v.x;
+                tot_e += v.y;
+                tot_s += v.z;
+            }
+            par ^= 1;
+            if (DIR) {
+                // - sum_k (alpha_k - 1) log(S' / S) with sum_k (alpha_k - 1) = 1 - K
+                const float x = tot_s * fast_rcp((float)dS_tot), lg = (float)(dK - 1) * log1p_k(x);
+                tot_e = x > -0.5f ? fmaf(2e-6f, fabsf(lg), 2.0f * tot_e) : INFINITY;
+                tot_c += lg;
+            }
+            // 4. the decision (identical in every thread): from the bound, or, too close
+            // to call (or Delta asked for), from every term's direct evaluation
+            double delta = (double)tot_c + (double)hast;
+            double dS = 0.0;
+            bool have_dS = false;
+            if (!decided(delta, logu, fmaf(1e-6f, fabsf(tot_c), tot_e))) {
+                double part = 0.0;
+                if (DIR) {
+                    const DirDelta dd = dir_delta(fr, cy, cx, d0);
+                    if (fr.n > 0.0f) {
+                        part = dd.tsum;
+                        dS = dd.dsum;
+                    }
+                    dS = wave_sum_dpp(dS);
+                    if (lane == 0) l.red2[wave] = dS;
+                }
+#pragma unroll 1
+                for (int e = threadIdx.x; e < F; e += NT) {
+                    const int i = origin + (e / s) * RW + e % s;
+                    const float m = l.mu[i];
+                    if (m < 0.0f) continue;
+                    part += delta_pix<EM>(m, mul_rn(d0, f.psf[SUB ? ph * F + e : e]), region_pc(i), inv_tab, nterms);
+                    ++ndirect;
+                }
+                part = wave_sum_dpp(part);
+                if (lane == 0) l.red[wave] = part;
+                lds_barrier();
+                delta = 0.0;
+                dS = 0.0;
+#pragma unroll 1
+                for (int w = 0; w < NW; ++w) {
+                    delta += l.red[w];
+                    if (DIR) dS += l.red2[w];
+                }
+                if (DIR) delta += (double)(dK - 1) * log1p(dS / dS_tot);
+                delta += (double)hast;
+                have_dS = true;
+            }
+            const bool acc = isfinite(delta) && ((double)logu < delta);
+            if (lane == lx) my_acc = acc;
+            if (want_delta && threadIdx.x == 0) {
+                const int64_t i = cell(ph, ly, lx);
+                if (dbg_delta) dbg_delta[i] = (float)delta;
+                if (dbg_acc) dbg_acc[i] = acc ? 1 : 0;
+            }
+            if (acc) {
+                ++n_acc;
+#pragma unroll
+                for (int q = 0; q < NQ; ++q)
+                    if (mq[q] >= 0.0f) l.mu[origin + off[q]] = fmaf(d0, pw[q], mq[q]);
+                if (DIR) {
+                    const DirDelta dd = dir_delta(fr, cy, cx, d0);
+                    if (!have_dS) {
+                        dS = wave_sum_dpp(fr.n > 0.0f ? dd.dsum : 0.0);
+                        if (lane == 0) l.red2[wave] = dS;
+                    }
+                    fr.re = fma((double)d0, dd.wr, fr.re);
+                    fr.im = fma((double)d0, dd.wi, fr.im);
+                    if (fr.n > 0.0f) dir_round();
+                }
+                // re-anchor the queued pixels at their new means
+                const int n = l.cnt[cq], id = threadIdx.x ^ (NT - 64);
+                if constexpr (EM) {
+                    for (int j = id; j < n; j += NT) anchor_em(l.job[j], l.job_mu[j]);
+                } else {
+                    for (int j = id >> 2; j < n; j += NT / 4) {
+                        const int i = l.job[j];
+                        const float m = l.job_mu[j];
+                        const Series sr = series_after(m, 0.0f, region_pc(i), id & 3, aterms);
+                        if ((id & 3) == 0) set_series(i, m, sr);
+                    }
+                }
+                lds_barrier();                                      // commits before the next footprint reads
+                if (DIR) {
+                    if (!have_dS) {
+                        dS = 0.0;
+#pragma unroll 1
+                        for (int w = 0; w < NW; ++w) dS += l.red2[w];
+                    }
+                    dS_tot += dS;
+                }
+            }
+            cq = cq1;
+        }
+        if (wave == 0 && lane >= lx0 && lane < lx1) {
+            const int64_t i = cell(ph, ly, lane);
+            if (my_acc) S.rho[i] = pr.x;
+            if (t < burn_in) S.log_step[i] = fmaf(gain, (my_acc ? 1.0f : 0.0f) - 0.44f, ls);
+        }
+        ph = nph;
+        ly = nly;
+        lx0 = nlx;
+    }
+    if (threadIdx.x == 0) atomicAdd(&S.accepts[chain], (unsigned long long)n_acc);
+    for (int i = threadIdx.x; i < NR; i += NT) {
+        const int y = i / RW, yy = ry0 + y, xx = rx0 + i - y * RW;
+        if (yy >= 0 && yy < f.Hp && xx >= 0 && xx < f.Wp) S.mu[pbase + (int64_t)yy * f.Wp + xx] = l.mu[i];
+    }
+    count_work5(S.counters, nterms, nevals, ndirect, nanch, aterms);
+}
+
+template <bool EM, bool DIR, bool SUB, int NT, int NQ>
+__global__ void __launch_bounds__(NT) k_block_bounded(Frame f, State S, int burn_in, const double* inv_tab, int B,
+                                                      int py, int px, int k0, int k1, float* dbg_delta,
+                                                      uint8_t* dbg_acc, int nblk) {
+    extern __shared__ double lds_d[];
+    int bi, chain;
+    if (!xcd_block(nblk, f.C, bi, chain)) return;
+    bounded_block<EM, DIR, SUB, NT, NQ>(f, S, burn_in, inv_tab, B, py, px, bi, chain, *S.t, k0, k1, dbg_delta,
+                                        dbg_acc, reinterpret_cast<char*>(lds_d));
+}
+
+// ---------------------------------------------------------------------------
 // Moments after a sweep: Welford over post-burn-in sweeps, per-batch
 // statistics (mean rho, mean and M2 of log rho) for R-hat and MCSE, and
 // per-workgroup partials of the log-posterior at the current mu.
@@ -2337,8 +2751,57 @@ static dim3 xcd_grid(int nblk, int C) {
     return dim3((unsigned)(XCDS * C * qx), (unsigned)((nq + qx - 1) / qx));
 }
 
+// The bounded pass takes the readings, priors and lattices that have no series
+// scan, with one cell per block and colour and a region within the LDS.  It was
+// the faster one at every size tried, from 100 x 134 (PSF 11, 3 chains: 1.8 against
+// 9.1 ms for two sweeps of the all-direct pass) to 1536^2 (PSF 31, 4 chains: 130 against
+// 1358 ms).  Larger blocks and regions keep the all-direct pass.
+static bool bounded_fits(const Frame& f, int B) {
+    if (!f.camera && !f.dir_am1 && f.sub == 1) return false;
+    if (f.dir_am1 && (f.sub > 1 || B != f.dir_B || B > DIR_MAX_B)) return false;
+    return B >= f.s - 1 && B >= 1 && B <= f.s && f.s * f.s <= BND_MAX_F &&
+           bounded_layout(B, f.s, f.camera != 0, f.dir_am1 != nullptr, nullptr, nullptr) <= BND_LDS_MAX;
+}
+
+template <bool EM, bool DIR, bool SUB, int NT, int NQ>
+static hipError_t launch_bounded_as(const Frame& f, const State& S, int burn_in, const double* inv_tab, int B,
+                                    int phase, int k0, int k1, float* dbg_delta, uint8_t* dbg_acc, hipStream_t st) {
+    const int py = phase / 2, px = phase % 2;
+    const int nby = (f.Hp + B - 1) / B, nbx = (f.Wp + B - 1) / B;
+    const int nblk = ((nby - py + 1) / 2) * ((nbx - px + 1) / 2);
+    if (nblk <= 0) return hipSuccess;
+    auto kern = k_block_bounded<EM, DIR, SUB, NT, NQ>;
+    static const hipError_t attr =
+        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)BND_LDS_MAX);
+    if (attr != hipSuccess) return attr;
+    const size_t lds = bounded_layout(B, f.s, EM, DIR, nullptr, nullptr);
+    hipLaunchKernelGGL(kern, xcd_grid(nblk, f.C), dim3(NT), lds, st, f, S, burn_in, inv_tab, B, py, px, k0, k1,
+                       dbg_delta, dbg_acc, nblk);
+    return hipGetLastError();
+}
+
+static hipError_t launch_bounded(const Frame& f, const State& S, int burn_in, const double* inv_tab, int B, int phase,
+                                 int k0, int k1, float* dbg_delta, uint8_t* dbg_acc, hipStream_t st) {
+    auto sized = [&](auto em, auto dir, auto sub) {
+        constexpr bool E = decltype(em)::value, D = decltype(dir)::value, U = decltype(sub)::value;
+        const int F = f.s * f.s;
+        auto go = [&](auto fn) { return fn(f, S, burn_in, inv_tab, B, phase, k0, k1, dbg_delta, dbg_acc, st); };
+        if (F <= 256) return go(launch_bounded_as<E, D, U, 256, 1>);
+        if (F <= 512) return go(launch_bounded_as<E, D, U, 512, 1>);
+        if (F <= 1024) return go(launch_bounded_as<E, D, U, 512, 2>);
+        if constexpr (!D) return go(launch_bounded_as<E, D, U, 512, 3>);
+        return hipErrorInvalidValue;
+    };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    if (f.sub > 1) return f.camera ? sized(yes, no, yes) : sized(no, no, yes);
+    if (f.dir_am1) return f.camera ? sized(yes, yes, no) : sized(no, yes, no);
+    return sized(yes, no, no);
+}
+
 hipError_t launch_block_phase(const Frame& f, const State& S, int burn_in, const double* inv_tab, int B,
                               int phase, int k0, int k1, float* dbg_delta, uint8_t* dbg_acc, hipStream_t st) {
+    if (bounded_fits(f, B)) return launch_bounded(f, S, burn_in, inv_tab, B, phase, k0, k1, dbg_delta, dbg_acc, st);
     if (f.sub > 1) {
         const int py = phase / 2, px = phase % 2;
         const int nby = (f.Hp + B - 1) / B, nbx = (f.Wp + B - 1) / B;
@@ -2355,22 +2818,7 @@ hipError_t launch_block_phase(const Frame& f, const State& S, int burn_in, const
     const int nby = (f.H + B - 1) / B, nbx = (f.W + B - 1) / B;
     const int nby_p = (nby - py + 1) / 2, nbx_p = (nbx - px + 1) / 2;
     if (nby_p <= 0 || nbx_p <= 0) return hipSuccess;
-    if (f.dir_am1) {
-        // the chunk prior couples a block's pixels: one pixel per block and colour
-        if (B != f.dir_B || B > f.s || B > DIR_MAX_B || f.s * f.s > SORT_MAX_F) return hipErrorInvalidValue;
-        const size_t lds = block_phase_lds(B, f.s) + dir_lds_bytes(B);
-        auto kern = f.camera ? k_block_phase_dir<true> : k_block_phase_dir<false>;
-        static bool attr_set[2] = {false, false};
-        if (!attr_set[f.camera ? 1 : 0]) {
-            hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               80 * 1024);
-            if (e != hipSuccess) return e;
-            attr_set[f.camera ? 1 : 0] = true;
-        }
-        hipLaunchKernelGGL(kern, xcd_grid(nby_p * nbx_p, f.C), dim3(WG), lds, st, f, S, burn_in, inv_tab,
-                           B, py, px, k0, k1, dbg_delta, dbg_acc, nby_p * nbx_p);
-        return hipGetLastError();
-    }
+    if (f.dir_am1) return hipErrorInvalidValue;              // one pixel per block and colour, B <= s <= 31
     hipLaunchKernelGGL(f.camera ? k_block_phase<true> : k_block_phase<false>, xcd_grid(nby_p * nbx_p, f.C),
                        dim3(WG), block_phase_lds(B, f.s), st, f, S, burn_in, inv_tab, B, py, px, k0, k1, dbg_delta,
                        dbg_acc, nby_p * nbx_p);
@@ -2602,7 +3050,7 @@ k_batch(const TileDesc* tiles, const Item* items, const double* inv_tab) {
         block_series_block(T.f, T.S, T.burn_in, T.B, ph / 2, ph % 2, I.index, I.chain, t, 0, T.f.s * T.f.s,
                            nullptr, nullptr, lds_b);
     } else if constexpr (KIND == BK_PHASE || KIND == BK_PHASE_EM) {
-        block_phase_block<false, KIND == BK_PHASE_EM>(T.f, T.S, T.burn_in, inv_tab, T.B, ph / 2, ph % 2, I.index,
+        block_phase_block<KIND == BK_PHASE_EM>(T.f, T.S, T.burn_in, inv_tab, T.B, ph / 2, ph % 2, I.index,
                                                       I.chain, t, 0, T.f.s * T.f.s, nullptr, nullptr, lds_b);
     } else if constexpr (KIND == BK_MOMENTS || KIND == BK_MOMENTS_EM) {
         moments_chunk<KIND == BK_MOMENTS_EM>(T.f, T.S, T.pr, T.M, T.burn_in, I.index, I.chain, t);

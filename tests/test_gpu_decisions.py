@@ -92,3 +92,83 @@ def test_sweeps_reach_the_state_of_direct_decisions(bdc, case):
     rb, lb, tb = B.rho()
     assert ta == tb == 6
     assert np.array_equal(ra, rb) and np.array_equal(la, lb)
+
+
+def lattice_frame(h, w, k, psf, seed, emccd, level, sharp):
+    """The same object on a k times finer lattice, read by either camera."""
+    from scipy import signal
+    rng = np.random.default_rng(seed)
+    obj = np.broadcast_to(np.linspace(1.0, 8.0, w * k)[None, :], (h * k, w * k)) / k ** 2
+    obj = obj.copy()
+    synth.add_beads(obj, rng, max(4, h * w // 150), scale=50.0 / k ** 2)
+    mu = np.clip(signal.fftconvolve(obj * level, psf, mode="same"), 1e-6, None)
+    phi = rng.poisson(mu.reshape(h, k, w, k).sum(axis=(1, 3)))
+    cam = synth.scmos_maps(rng, h, w)
+    if sharp:
+        cam.sigma[:, :w // 2] = sharp
+    g, o, sg = cam.maps(h, w)
+    if emccd:
+        img = o + g * np.where(phi > 0, rng.gamma(np.maximum(phi, 1), 1.0), 0.0)
+        return img + np.where(phi == 0, sg * rng.standard_normal((h, w)), 0.0), cam
+    return g * phi + o + sg * rng.standard_normal((h, w)), cam
+
+
+# One cell per block and colour, without a series scan of its own: the EMCCD reading, the chunk prior, a finer lattice.
+# Footprints on both sides of every launch size (F = 256, 512, 1024, 1536 terms; pixel side 33 at k = 2 and PSF 63),
+# blocks of s - 1, and one region (EMCCD, side 37) beyond the LDS, which takes the direct pass.
+BOUNDED_CASES = [
+    # (EMCCD, chunk prior, k, psf, block, h, w, level, read noise of the left half where not 0)
+    (1, 0, 1, ("gauss", 3), 3, 20, 31, 1.0, 0.0),
+    (1, 0, 1, ("gauss", 11), 0, 40, 37, 0.05, 0.0),
+    (1, 0, 1, ("gauss", 15), 14, 45, 50, 20.0, 0.0),
+    (1, 0, 1, ("airy", 17), 0, 40, 61, 1.0, 0.1),
+    (1, 0, 1, ("airy", 23), 22, 50, 60, 1.0, 0.0),
+    (1, 0, 1, ("airy", 33), 0, 70, 67, 5.0, 0.0),
+    (1, 0, 1, ("gauss", 37), 0, 75, 80, 1.0, 0.0),
+    (0, 1, 1, ("gauss", 3), 2, 19, 22, 1.0, 0.0),
+    (0, 1, 1, ("gauss", 11), 0, 37, 45, 0.1, 0.15),
+    (0, 1, 1, ("gauss", 15), 14, 44, 43, 30.0, 0.0),
+    (0, 1, 1, ("airy", 21), 20, 50, 61, 1.0, 0.0),
+    (0, 1, 1, ("airy", 31), 0, 63, 80, 1.0, 0.0),
+    (1, 1, 1, ("gauss", 15), 0, 40, 47, 1.0, 0.0),
+    (1, 1, 1, ("airy", 31), 30, 64, 70, 2.0, 0.0),
+    (0, 0, 2, ("gauss", 15), 0, 30, 33, 1.0, 0.0),
+    (0, 0, 2, ("airy", 31), 0, 40, 45, 10.0, 0.15),
+    (0, 0, 2, ("airy", 63), 0, 70, 68, 1.0, 0.0),
+    (0, 0, 3, ("gauss", 31), 0, 30, 29, 0.1, 0.0),
+    (1, 0, 2, ("airy", 41), 0, 50, 47, 1.0, 0.0),
+    (1, 0, 2, ("airy", 63), 0, 67, 66, 1.0, 0.0),
+]
+
+
+@pytest.mark.parametrize("case", BOUNDED_CASES,
+                         ids=lambda c: "em%d-dir%d-k%d-%s%d-B%d-%gx%g" % (*c[:3], *c[3], c[4], *c[7:]))
+def test_bounded_block_sweeps_reach_the_state_of_direct_decisions(bdc, case):
+    em, chunk, k, (kind, s), block, h, w, level, sharp = case
+    psf = synth.gaussian_psf(max(0.5, (s - 1) / 8.0), s) if kind == "gauss" else synth.airy_psf_matched(s / 10.0, s)
+    img, cam = lattice_frame(h, w, k, psf, 11 + s + h, em, level, sharp)
+    A, B = twins(bdc, img, cam, psf, bdc.BDC_SCHED_BLOCK, block, 2, 5 + s, 3, camera=em, object_sub=k,
+                 prior_kind=bdc.BDC_PRIOR_DIRICHLET if chunk else bdc.BDC_PRIOR_FLAT)
+    A.profile_read()
+    A.sweep(4)
+    work = A.profile_read()[2]
+    print(case, "direct evaluations %d of %d" % (work[2], work[1]), flush=True)
+    advance_by_groups(B, 4)
+    ra, la, ta = A.rho()
+    rb, lb, tb = B.rho()
+    assert ta == tb == 4
+    assert np.array_equal(ra, rb) and np.array_equal(la, lb)
+
+
+def test_colour_ranges_of_the_bounded_block_pass(bdc):
+    """Group ranges cut anywhere (mid-row, mid-phase) visit every cell once between them."""
+    psf = synth.gaussian_psf(1.5, 11)
+    img, cam = lattice_frame(29, 34, 2, psf, 3, 1, 1.0, 0.0)
+    A, B = twins(bdc, img, cam, psf, bdc.BDC_SCHED_BLOCK, 0, 2, 9, 3, camera=1, object_sub=2)
+    n = A.schedule_info()[0]
+    cuts = [0, 7, n // 3, n // 3 + 1, n // 2 + 5, n]
+    visits = np.zeros((2, 58, 68), int)
+    for a, b in zip(cuts[:-1], cuts[1:]):
+        visits += B.run_groups(a, b)[1] != 255
+    assert np.all(visits == 1)
+    assert np.all(A.run_groups(0, n)[1] != 255)

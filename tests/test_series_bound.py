@@ -155,3 +155,61 @@ def test_intervals_outside_the_radius(c, a, mu, sign):
     for lower, upper in log_moment_intervals(c, a, mu, v):
         assert np.all(exact >= lower - slack), (exact - lower).min()
         assert np.all(exact <= upper + slack), (upper - exact).min()
+
+
+# EMCCD reading: f(mu) = sqrt(mu / c) I_1(2 sqrt(mu c)), whose zeros in mu are 0 and
+# -j^2 / (4 c) (j the zeros of J_1), so that log f(mu (1 + v)) / f(mu) is a sum of
+# log(1 + beta v), 0 < beta <= 1, and the intervals above hold for it.
+
+def em_log_f(mu, c):
+    from scipy.special import ive
+    z = 2.0 * np.sqrt(mu * c)
+    return 0.5 * np.log(mu / c) + np.log(ive(1, z)) + z
+
+
+def em_coefficients(mu, c):
+    """h_1..h_4 of log f in v: from f' = I_0, f'' = (c / mu) f below z = 16, from Hankel's
+    series of I_1 above, as the kernel forms them."""
+    from scipy.special import ive
+    q = mu * c
+    z = 2.0 * np.sqrt(q)
+    if z < 16.0:
+        e = 0.5 * z * ive(0, z) / ive(1, z)
+        s = [1.0, e, 0.5 * q, q * (e - 1.0) / 6.0, q * (q - 2.0 * e + 2.0) / 24.0]
+        h = [0.0] * 5
+        for j in range(1, 5):
+            h[j] = s[j] - sum(i * h[i] * s[j - i] for i in range(1, j)) / j
+        return np.array(h[1:])
+    half = np.array([0.5, -0.125, 0.0625, -0.0390625])
+    log = np.array([1.0, -0.5, 1.0 / 3.0, -0.25])
+    power = lambda a: np.array([a, a * (a - 1) / 2, a * (a - 1) * (a - 2) / 6, a * (a - 1) * (a - 2) * (a - 3) / 24])
+    return (z * half + 0.25 * log - 0.375 / z * power(-0.5) - 0.1875 / z ** 2 * power(-1.0) -
+            0.1640625 / z ** 3 * power(-1.5) - 0.2109 / z ** 4 * power(-2.0))
+
+
+@pytest.mark.parametrize("mu,c", [(0.02, 0.5), (0.5, 0.01), (2.0, 3.0), (7.9, 8.0), (8.1, 8.0), (30.0, 25.0),
+                                  (400.0, 500.0), (1e4, 9e3)])
+def test_emccd_intervals(mu, c):
+    h = em_coefficients(mu, c)
+    e, s2, p3, p4 = h[0], -2.0 * h[1], 3.0 * h[2], -4.0 * h[3]
+    assert e >= s2 >= p3 >= p4 > 0.0 or mu * c < 1e-2    # sums of falling powers of beta
+    for sign in (1, -1):
+        v = sign * np.concatenate([np.geomspace(1e-3, 0.97, 60)] + ([np.geomspace(1.0, 40.0, 30)] if sign > 0 else []))
+        exact = em_log_f(mu * (1.0 + v), c) - em_log_f(mu, c)
+        r4 = np.log1p(v) - v + v ** 2 / 2 - v ** 3 / 3 + v ** 4 / 4
+        r3 = r4 - v ** 4 / 4
+        t3 = e * v - s2 * v ** 2 / 2 + p3 * v ** 3 / 3
+        t4 = t3 - p4 * v ** 4 / 4
+        lower = t3 + p3 * r3 if sign > 0 else t4 + p4 * r4
+        upper = t3 + p4 * r3 if sign > 0 else t4
+        # the kernel's own margin: 4e-6 of E |v|, over 1 - |v| for v < 0
+        slack = 4e-6 * e * np.abs(v) / np.where(v < 0, 1.0 + v, 1.0) + 1e-12 * (1.0 + np.abs(em_log_f(mu, c)))
+        assert np.all(exact >= lower - slack), (exact - lower).min()
+        assert np.all(exact <= upper + slack), (upper - exact).min()
+        if sign > 0:
+            big = v >= 1.0
+            assert np.all(exact[big] >= (e * e / s2 * np.log1p(s2 * v / e) - slack)[big])
+            assert np.all(exact[big] <= ((e - s2) * v + s2 * np.log1p(v) + slack)[big])
+        near = np.abs(v) <= 0.5
+        u = np.abs(v[near])
+        assert np.all(np.abs(exact - t4)[near] <= p4 / 5 * u ** 5 / (1 - u) + slack[near])
