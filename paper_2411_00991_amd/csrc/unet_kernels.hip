@@ -17,6 +17,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <type_traits>
+
+#include "bdc_consts.h"
 #include "unet.h"
 
 namespace bdc {
@@ -37,6 +41,13 @@ __device__ inline uint16_t f2bf(float f) {
     const uint32_t u = __float_as_uint(f);
     if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x007FFFFFu)) return (uint16_t)((u >> 16) | 0x40);
     return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+}
+
+// Two of them, by the conversion instruction (also to nearest even).
+__device__ inline uint32_t bf2(float a, float b) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const bf16x2 v = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(uint32_t, v);
 }
 
 __device__ inline void pixel_of(int64_t m, int H, int W, int& b, int& y, int& x) {
@@ -124,6 +135,21 @@ struct OpPlain {
     }
 };
 
+// Weights of a 3x3 layer whose channels come in slabs of 32, in fragment order: the MFMA
+// operands of 16 rows x 32 k, lane (k / 8 % 4, row) holding 8 k.  Rows 4 g + e of the
+// fragments j = 0, 1 of a pair are channels 8 g + 4 j + e of its 32.
+__host__ __device__ inline int64_t frag_at(int n, int k, int K) {
+    const int64_t row = ((int64_t)((n >> 5) * 2 + ((n >> 2) & 1)) * (K >> 5) * 64 + ((n >> 3) & 3) * 4 + (n & 3)) * 8;
+    return row + (k >> 5) * 512 + ((k >> 3) & 3) * 128 + (k & 7);
+}
+struct OpFrag {
+    const uint16_t* p; int N, K;
+    // (rows past N: the last ones, not stored)
+    __device__ bf16x8 frag(int f, int k32, int lane) const {
+        return *(const bf16x8*)(p + (((int64_t)min(f, (N >> 4) - 1) * (K >> 5) + k32) * 64 + lane) * 8);
+    }
+};
+
 // ---------------------------------------------------------------------------
 // K-major operand policies (weight gradients, K = pixels): load_t(r0, k) gives
 // rows r0..r0+7 at column k (zero outside).
@@ -193,14 +219,28 @@ struct EpAct {
     static constexpr bool kStaged = true;
     uint16_t* p; int ld, off; const float* bias; int relu;
     const uint16_t* mask; int mld, moff;      // gradient through a ReLU: keep where mask > 0
-    __device__ float act(int64_t, int n, float v) const {
-        if (bias) v += bias[n];
+    __device__ float act(int64_t, int n, float v) const { return act(bias ? bias[n] : 0.0f, v); }
+    __device__ float act(float b, float v) const {
+        if (bias) v += b;
         return relu ? fmaxf(v, 0.0f) : v;
     }
     __device__ void store(int64_t m, int n, float v) const {
         v = act(m, n, v);
         if (mask && !(bf2f(mask[m * mld + moff + n]) > 0.0f)) v = 0.0f;
         p[m * ld + off + n] = f2bf(v);
+    }
+    // columns n .. n+3 of row m, already activated, as 4 BF16
+    __device__ void store4(int64_t m, int n, uint2 v) const {
+        if (mask) {
+            const uint2 k = *(const uint2*)(mask + m * mld + moff + n);
+            auto keep = [](uint32_t w) {
+                return (bf2f((uint16_t)(w & 0xFFFF)) > 0.0f ? 0x0000FFFFu : 0u) |
+                       (bf2f((uint16_t)(w >> 16)) > 0.0f ? 0xFFFF0000u : 0u);
+            };
+            v.x &= keep(k.x);
+            v.y &= keep(k.y);
+        }
+        *(uint2*)(p + m * ld + off + n) = v;
     }
     // columns n .. n+7 of row m, already activated, as 8 BF16
     __device__ void store8(int64_t m, int n, uint4 v) const {
@@ -311,7 +351,14 @@ __device__ inline bf16x8 frag_kmajor(const uint16_t* lds, int row, int g) {
 // Epilogue through LDS: the activated tile is staged as BF16 ([BM][BN + 8]) so
 // that every thread writes whole 16-byte rows of 8 channels.  Needs N % 8 == 0
 // and 16-byte aligned rows in the destination.
-template <int BM, int BN, class EP, int TM, int TN>
+// Column of the tile that a wave's fragment j holds in lane column r16.
+template <int BN, bool FRAG>
+__device__ inline int tile_col(int wn, int j, int r16) {
+    const int f = wn * (BN / 32) + j;
+    return FRAG ? (f >> 1) * 32 + (f & 1) * 4 + (r16 >> 2) * 8 + (r16 & 3) : f * 16 + r16;
+}
+
+template <int BM, int BN, bool FRAG, class EP, int TM, int TN>
 __device__ inline void staged_epilogue(const EP& ep, const f32x4 (&acc)[TM][TN], uint16_t* stage, int64_t m0, int n0,
                                        int64_t M, int N, int wm, int wn, int g, int r16) {
     constexpr int SP = BN + 8;
@@ -321,7 +368,7 @@ __device__ inline void staged_epilogue(const EP& ep, const f32x4 (&acc)[TM][TN],
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int rm = wm * (BM / 2) + i * 16 + g * 4 + e, rn = wn * (BN / 2) + j * 16 + r16;
+                const int rm = wm * (BM / 2) + i * 16 + g * 4 + e, rn = tile_col<BN, FRAG>(wn, j, r16);
                 const int n = n0 + rn;
                 stage[rm * SP + rn] = f2bf(n < N ? ep.act(m0 + rm, n, acc[i][j][e]) : 0.0f);
             }
@@ -336,6 +383,7 @@ __device__ inline void staged_epilogue(const EP& ep, const f32x4 (&acc)[TM][TN],
 template <int BM, int BN, class OA, bool AT, class OB, bool BT, class EP>
 __global__ void __launch_bounds__(NT) k_gemm(OA oa, OB ob, EP ep, int64_t M, int N, int64_t K, int64_t kchunk) {
     constexpr int TM = BM / 32, TN = BN / 32;
+    constexpr bool kFrag = std::is_same_v<OB, OpFrag>;
     constexpr int CA = (BM * 4 + NT - 1) / NT, CB = (BN * 4 + NT - 1) / NT;
     // operand tiles (double-buffered); reused as the epilogue's staging tile
     __shared__ __attribute__((aligned(16))) uint16_t s_buf[2 * (BM + BN) * BKP];
@@ -355,7 +403,7 @@ __global__ void __launch_bounds__(NT) k_gemm(OA oa, OB ob, EP ep, int64_t M, int
 #pragma unroll
         for (int q = 0; q < CA; ++q) rca[q] = oa.prep(m0 + ((threadIdx.x + q * NT) >> 2));
     }
-    if constexpr (!BT) {
+    if constexpr (!BT && !kFrag) {
 #pragma unroll
         for (int q = 0; q < CB; ++q) rcb[q] = ob.prep((int64_t)n0 + ((threadIdx.x + q * NT) >> 2));
     }
@@ -367,16 +415,25 @@ __global__ void __launch_bounds__(NT) k_gemm(OA oa, OB ob, EP ep, int64_t M, int
         for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
     uint4 ra[CA], rb[CB];
+    const int g = lane >> 4, r16 = lane & 15;
+    // weights in fragment order go straight to registers, one step ahead (frames whose
+    // levels have no whole tiles, 320 x 440: 0.64 -> 0.57 ms; two steps ahead: 0.72, the
+    // registers cost a wave per SIMD)
+    bf16x8 fb_next[TN];
     auto fetch = [&](int64_t k0) {
         if constexpr (AT) stage_cols_fetch<BM>(oa, (int)m0, k0, ke, ra);
         else stage_rows_fetch<BM>(oa, rca, k0, ke, ra);
-        if constexpr (BT) stage_cols_fetch<BN>(ob, n0, k0, ke, rb);
+        if constexpr (kFrag) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fb_next[j] = ob.frag((n0 >> 4) + wn * TN + j, (int)(k0 >> 5), lane);
+        } else if constexpr (BT) stage_cols_fetch<BN>(ob, n0, k0, ke, rb);
         else stage_rows_fetch<BN>(ob, rcb, k0, ke, rb);
     };
     auto put = [&](int buf) {
         if constexpr (AT) stage_cols_store<BM>(sA[buf], ra);
         else stage_rows_store<BM>(sA[buf], ra);
-        if constexpr (BT) stage_cols_store<BN>(sB[buf], rb);
+        if constexpr (kFrag) return;
+        else if constexpr (BT) stage_cols_store<BN>(sB[buf], rb);
         else stage_rows_store<BN>(sB[buf], rb);
     };
 
@@ -386,11 +443,14 @@ __global__ void __launch_bounds__(NT) k_gemm(OA oa, OB ob, EP ep, int64_t M, int
         put(0);
     }
     __syncthreads();
-    const int g = lane >> 4, r16 = lane & 15;
     for (int s = 0; s < nsteps; ++s) {
         const int buf = s & 1;
-        if (s + 1 < nsteps) fetch(kb + (int64_t)(s + 1) * BK);
         bf16x8 fa[TM], fb[TN];
+        if constexpr (kFrag) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fb[j] = fb_next[j];
+        }
+        if (s + 1 < nsteps) fetch(kb + (int64_t)(s + 1) * BK);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             if constexpr (AT) fa[i] = frag_kmajor<BM>(sA[buf], wm * (BM / 2) + i * 16 + r16, g);
@@ -398,7 +458,8 @@ __global__ void __launch_bounds__(NT) k_gemm(OA oa, OB ob, EP ep, int64_t M, int
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            if constexpr (BT) fb[j] = frag_kmajor<BN>(sB[buf], wn * (BN / 2) + j * 16 + r16, g);
+            if constexpr (kFrag) continue;
+            else if constexpr (BT) fb[j] = frag_kmajor<BN>(sB[buf], wn * (BN / 2) + j * 16 + r16, g);
             else fb[j] = *(const bf16x8*)(sB[buf] + (wn * (BN / 2) + j * 16 + r16) * BKP + g * 8);
         }
 #pragma unroll
@@ -412,7 +473,7 @@ __global__ void __launch_bounds__(NT) k_gemm(OA oa, OB ob, EP ep, int64_t M, int
     // D layout: lane holds rows 4 * (lane / 16) + e of column lane % 16.
     if constexpr (EP::kStaged) {
         if (N % 8 == 0) {            // uniform: the loop above ended with a barrier
-            staged_epilogue<BM, BN>(ep, acc, s_buf, m0, n0, M, N, wm, wn, g, r16);
+            staged_epilogue<BM, BN, kFrag>(ep, acc, s_buf, m0, n0, M, N, wm, wn, g, r16);
             return;
         }
     }
@@ -423,7 +484,7 @@ __global__ void __launch_bounds__(NT) k_gemm(OA oa, OB ob, EP ep, int64_t M, int
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int64_t m = m0 + wm * (BM / 2) + i * 16 + g * 4 + e;
-                const int n = n0 + wn * (BN / 2) + j * 16 + r16;
+                const int n = n0 + tile_col<BN, kFrag>(wn, j, r16);
                 if (m < M && n < N) ep.store(m, n, acc[i][j][e]);
             }
 }
@@ -475,125 +536,177 @@ hipError_t gemm_wgrad(const OA& oa, const OB& ob, float* part, int M, int N, int
 }
 
 // ---------------------------------------------------------------------------
-// 3x3 convolution with the input tile staged once per 32-channel slab.  An
-// output tile of TH x TW pixels (128) x BN channels; for each slab of 32 input
-// channels the (TH + 2) x (TW + 2) halo is loaded into LDS (zero outside the
-// image, pixel pitch 40 elements: the 16 pixels one MFMA row-group reads fall
-// in distinct banks), then the nine taps read their A fragments from it and
-// their B fragments (weights, [c_out][tap][c_in]) straight from the L2.
-// Every input pixel is read once per slab instead of once per tap.
+// 3x3 convolution with the input tile staged once per 32-channel slab.  A wave
+// owns 16 x 4 output pixels x 16 TN channels; WX x WY x WN waves make a workgroup
+// of 16 WX x 4 WY pixels x 16 TN WN channels, which goes over the tiles of its share of
+// the image.  For each slab of 32 input channels the halo is loaded into LDS (zero
+// outside the image, pixel pitch 40 elements: the 16 pixels that one MFMA operand
+// reads fall in distinct banks); a wave takes its 6 rows x 3 shifts of pixel fragments
+// from there once and runs the nine taps from registers, so a fragment serves the up to
+// three taps that see its row, while the next slab's (or tile's) halo is in flight.
+// Weight fragments come from the L2 in the order in which they are used, 1 KB each, two
+// taps ahead.  The weights are the MFMA's rows, so that a lane ends with 4 (of a pair of
+// fragments 8) consecutive channels of one pixel and stores them as they are.
+// Accumulation per output: slab by slab, tap by tap, 32 channels each.
+//
+// What bounds it: the MFMA units with what their operands take, LDS (18 KB a wave and
+// slab) and L1 (weights: 1 KB for four MFMA of each wave, 64 bytes a clock); the first
+// level also HBM.  At 2048^2 (levels of 32, 64, 128, 256 channels), us before (taps reading
+// LDS each, row-major weights without a lead, tile staged for the store) and now:
+// 32 -> 32 channels 203 -> 160, 64 -> 32 465 -> 283, 64 -> 64 at half the side 205 -> 119, 128 -> 64
+// 356 -> 209, 128 -> 128 at a quarter 177 -> 98, 256 -> 128 313 -> 180 (860 TFLOP/s).  Row-major
+// weights cost 25 to 60 % more, eight rows a wave (one wave per SIMD) 20 to 45 %.
 // ---------------------------------------------------------------------------
 constexpr int HALO_PP = 40;        // LDS elements per halo pixel (32 channels + pad)
 
-// ONE: a single 32-channel slab (C = 32), whose halo needs no second buffer,
-// so the workgroup holds half the LDS and more of them fit on a CU.
-template <int BN, int TW, class EP, bool ONE>
-__global__ void __launch_bounds__(NT) k_conv3_halo(Tens x, const uint16_t* wf, int K, EP ep, int N) {
-    constexpr int TH = 128 / TW, HW = TW + 2, HH = TH + 2;
-    constexpr int TM = 4, TN = BN / 32;
-    constexpr int HALO = HH * HW * HALO_PP;
-    constexpr int STAGE = 128 * (BN + 8);
-    constexpr int NBUF = ONE ? 1 : 2;
-    __shared__ __attribute__((aligned(16))) uint16_t s_buf[(NBUF * HALO > STAGE) ? NBUF * HALO : STAGE];
-    const int tiles_x = x.W / TW, tiles_y = x.H / TH;
-    const int tx = blockIdx.x % tiles_x, rest = blockIdx.x / tiles_x;
-    const int ty = rest % tiles_y, b = rest / tiles_y;
-    const int y0 = ty * TH, x0 = tx * TW;
-    const int n0 = blockIdx.y * BN;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
+inline bool frag_order(int ci, int co) { return ci % 32 == 0 && co % 32 == 0; }
+
+// waves per SIMD that the shape's registers leave
+constexpr int halo_waves(int tm, int tn) { return tm == 8 ? 1 : tn == 1 ? 4 : tn == 2 ? 3 : 2; }
+
+template <int TM, int TN, int WX, int WY, int WN, class EP>
+__global__ void __launch_bounds__(64 * WX * WY * WN) __attribute__((amdgpu_waves_per_eu(halo_waves(TM, TN))))
+k_conv3_halo(Tens x, const uint16_t* wf, int K, EP ep, int N,
+                                                                  int tiles) {
+    constexpr int NTH = 64 * WX * WY * WN, TW = 16 * WX, TH = TM * WY, HW = TW + 2, HH = TH + 2, BN = 16 * TN * WN;
+    __shared__ __attribute__((aligned(16))) uint16_t s_buf[HH * HW * HALO_PP];
+    const int tiles_x = (x.W + TW - 1) / TW, tiles_y = (x.H + TH - 1) / TH;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wn = wave % WN, wx = wave / WN % WX, wy = wave / WN / WX;
     const int g = lane >> 4, r16 = lane & 15;
-    const int C = x.C;
+    const int nf0 = blockIdx.y * (BN / 16) + wn * TN;              // this wave's first weight fragment row
+
+    // tiles in runs of consecutive ones per die, whose L2 then serves the halos' overlap
+    const int die = blockIdx.x % XCDS, run = (tiles + XCDS - 1) / XCDS;
+    const int stride = gridDim.x / XCDS, end = min(tiles, (die + 1) * run);
+    int tile = die * run + blockIdx.x / XCDS;
+    if (tile >= end) return;
 
     // a slab's halo in two steps: every load of this thread issued into
     // registers first, then the LDS stores, so the loads are in flight
-    // together (and, for the next slab, during this slab's taps)
-    constexpr int NCH = HH * HW * 4, NIT = (NCH + NT - 1) / NT;
+    // together and during the taps of the slab before
+    constexpr int NCH = HH * HW * 4, NIT = (NCH + NTH - 1) / NTH;
     uint4 hv[NIT];
-    auto halo_issue = [&](int c0) {
+    auto halo_issue = [&](int tl, int c0) {
+        const int tx = tl % tiles_x, rest = tl / tiles_x, ty = rest % tiles_y, b = rest / tiles_y;
+        const uint16_t* p = x.p + (((int64_t)b * x.H + ty * TH - 1) * x.W + tx * TW - 1) * x.ld + x.off + c0;
 #pragma unroll
         for (int k = 0; k < NIT; ++k) {
-            const int c = threadIdx.x + k * NT;
+            const int c = threadIdx.x + k * NTH;
             const int pix = c >> 2, q = c & 3;
             const int hy = pix / HW, hx = pix - hy * HW;
-            const int yy = y0 + hy - 1, xx = x0 + hx - 1;
+            const int yy = ty * TH + hy - 1, xx = tx * TW + hx - 1;
             hv[k] = make_uint4(0, 0, 0, 0);
             if (c < NCH && yy >= 0 && yy < x.H && xx >= 0 && xx < x.W)
-                hv[k] = *(const uint4*)(x.p + (((int64_t)b * x.H + yy) * x.W + xx) * x.ld + x.off + c0 + q * 8);
+                hv[k] = *(const uint4*)(p + ((int64_t)hy * x.W + hx) * x.ld + q * 8);
         }
     };
-    auto halo_commit = [&](uint16_t* h) {
+    auto halo_commit = [&]() {
 #pragma unroll
         for (int k = 0; k < NIT; ++k) {
-            const int c = threadIdx.x + k * NT;
-            if (c < NCH) *(uint4*)(h + (c >> 2) * HALO_PP + (c & 3) * 8) = hv[k];
+            const int c = threadIdx.x + k * NTH;
+            if (c < NCH) *(uint4*)(s_buf + (c >> 2) * HALO_PP + (c & 3) * 8) = hv[k];
         }
     };
 
-    f32x4 acc[TM][TN];
+    // weight fragment of row group j, tap t, slab sl (groups past N: the last one's)
+    const int nslab = x.C / 32;
+    const uint16_t* wj[TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j) wj[j] = wf + ((int64_t)min(nf0 + j, (N >> 4) - 1) * (K >> 5) * 64 + lane) * 8;
+    constexpr int AHEAD = 2, RING = AHEAD + 1;
+    bf16x8 fw[RING][TN];
+    auto fetch_w = [&](int slot, int sl, int t) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int j = 0; j < TN; ++j) fw[slot][j] = *(const bf16x8*)(wj[j] + (t * nslab + sl) * 512);
+    };
 
-    const int nslab = ONE ? 1 : C / 32;
-    halo_issue(0);
-    halo_commit(s_buf);
-    __syncthreads();
-    for (int sl = 0; sl < nslab; ++sl) {
-        uint16_t* h = s_buf + (sl & 1) * HALO;
-        if (sl + 1 < nslab) halo_issue((sl + 1) * 32);
-#pragma unroll 1
-        for (int t = 0; t < 9; ++t) {
-            const int dy = t / 3, dx = t % 3;        // halo offsets of this tap
-            bf16x8 fa[TM], fb[TN];
+    halo_issue(tile, 0);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int n = n0 + wn * (BN / 2) + j * 16 + r16;
-                fb[j] = n < N ? *(const bf16x8*)(wf + (int64_t)n * K + t * C + sl * 32 + g * 8) : bf16x8{};
+    for (int t = 0; t < AHEAD; ++t) fetch_w(t, 0, t);
+    halo_commit();
+    __syncthreads();
+    while (true) {
+        f32x4 acc[TM][TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        const int cur = tile;
+        bool more = true;
+        for (int sl = 0; sl < nslab; ++sl) {
+            const bool last = sl + 1 == nslab;
+            const int nsl = last ? 0 : sl + 1;
+            if (last) {
+                tile += stride;
+                more = tile < end;
             }
+            if (more) halo_issue(tile, nsl * 32);
+            bf16x8 fa[TM + 2][3];
+#pragma unroll
+            for (int h = 0; h < TM + 2; ++h)
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+                    fa[h][dx] = *(const bf16x8*)(s_buf + ((wy * TM + h) * HW + wx * 16 + r16 + dx) * HALO_PP + g * 8);
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                // (nine taps are three rounds of the ring: a slab starts at slot 0)
+                const int tn = t + AHEAD;
+                fetch_w(tn % RING, tn < 9 ? sl : nsl, tn % 9);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[t % RING][j], fa[i + t / 3][t % 3],
+                                                                            acc[i][j], 0, 0, 0);
+            }
+            if (more) {
+                __syncthreads();                                    // every wave has its fragments
+                halo_commit();
+                __syncthreads();
+            }
+        }
+        // lane: pixel r16 of each of the wave's rows, rows 4 g + e of each fragment: channels
+        // 32 p + 8 g + 4 j + e of fragment 2 p + j
+        const int tx = cur % tiles_x, rest = cur / tiles_x, ty = rest % tiles_y, b = rest / tiles_y;
+        const int xx = tx * TW + wx * 16 + r16;
+        constexpr int PJ = TN >= 2 ? 2 : 1;
+#pragma unroll
+        for (int j = 0; j < TN; j += PJ) {
+            const int n = ((nf0 + j) >> 1) * 32 + g * 8 + ((nf0 + j) & 1) * 4;
+            if (nf0 + j >= (N >> 4)) continue;
+            float bv[4 * PJ];
+#pragma unroll
+            for (int e = 0; e < 4 * PJ; ++e) bv[e] = ep.bias ? ep.bias[n + e] : 0.0f;
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
-                const int r = wm * 64 + i * 16 + r16;                  // output pixel in the tile
-                const int py = r / TW, px = r - (r / TW) * TW;
-                fa[i] = *(const bf16x8*)(h + ((py + dy) * HW + px + dx) * HALO_PP + g * 8);
+                const int yy = ty * TH + wy * TM + i;
+                if (yy >= x.H || xx >= x.W) continue;
+                uint32_t v[2 * PJ];
+#pragma unroll
+                for (int e = 0; e < 2 * PJ; ++e) {
+                    const f32x4& d = acc[i][j + e / 2];
+                    v[e] = bf2(ep.act(bv[2 * e], d[2 * (e & 1)]), ep.act(bv[2 * e + 1], d[2 * (e & 1) + 1]));
+                }
+                const int64_t m = ((int64_t)b * x.H + yy) * x.W + xx;
+                if constexpr (PJ == 2) ep.store8(m, n, make_uint4(v[0], v[1], v[2], v[3]));
+                else ep.store4(m, n, make_uint2(v[0], v[1]));
             }
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
         }
-        if (sl + 1 < nslab) halo_commit(s_buf + ((sl + 1) & 1) * HALO);
-        __syncthreads();
+        if (!more) break;
     }
-    // output rows: tile pixel r -> image pixel (b, y0 + r / TW, x0 + r % TW)
-    struct EpTile {
-        const EP& e; int b, y0, x0, H, W;
-        __device__ int64_t pix(int r) const {
-            return ((int64_t)b * H + y0 + r / TW) * W + x0 + r % TW;
-        }
-        __device__ float act(int64_t r, int n, float v) const { return e.act(pix((int)r), n, v); }
-        __device__ void store8(int64_t r, int n, uint4 v) const { e.store8(pix((int)r), n, v); }
-    } et{ep, b, y0, x0, x.H, x.W};
-    staged_epilogue<128, BN>(et, acc, s_buf, 0, n0, 128, N, wm, wn, g, r16);
 }
 
-template <int BN, class EP>
-hipError_t conv_halo_bn(const Tens& x, const uint16_t* wf, int K, const EP& ep, int N, int64_t P, hipStream_t st) {
-    const int TW = x.W % 32 == 0 ? 32 : (x.W % 16 == 0 ? 16 : 8);
-    const int TH = 128 / TW;
-    const unsigned tiles = (unsigned)((int64_t)(x.W / TW) * (x.H / TH) * (P / ((int64_t)x.H * x.W)));
-    const dim3 grid(tiles, (unsigned)((N + BN - 1) / BN));
-    if (x.C == 32) {
-        if (TW == 32) hipLaunchKernelGGL((k_conv3_halo<BN, 32, EP, true>), grid, dim3(NT), 0, st, x, wf, K, ep, N);
-        else if (TW == 16) hipLaunchKernelGGL((k_conv3_halo<BN, 16, EP, true>), grid, dim3(NT), 0, st, x, wf, K, ep, N);
-        else hipLaunchKernelGGL((k_conv3_halo<BN, 8, EP, true>), grid, dim3(NT), 0, st, x, wf, K, ep, N);
-    } else {
-        if (TW == 32) hipLaunchKernelGGL((k_conv3_halo<BN, 32, EP, false>), grid, dim3(NT), 0, st, x, wf, K, ep, N);
-        else if (TW == 16) hipLaunchKernelGGL((k_conv3_halo<BN, 16, EP, false>), grid, dim3(NT), 0, st, x, wf, K, ep, N);
-        else hipLaunchKernelGGL((k_conv3_halo<BN, 8, EP, false>), grid, dim3(NT), 0, st, x, wf, K, ep, N);
-    }
+template <int TM, int TN, int WX, int WY, int WN, class EP>
+hipError_t conv_halo_as(const Tens& x, const uint16_t* wf, int K, const EP& ep, int N, int64_t P, hipStream_t st) {
+    const int tx = (x.W + 16 * WX - 1) / (16 * WX), ty = (x.H + TM * WY - 1) / (TM * WY);
+    const int BN = 16 * TN * WN, ny = (N + BN - 1) / BN;
+    const int64_t tiles = (int64_t)tx * ty * (P / ((int64_t)x.H * x.W));
+    if (tiles > (1 << 30)) return hipErrorInvalidValue;
+    // workgroups: a multiple of the dies, no more than are resident
+    const int64_t groups = std::min<int64_t>((tiles + XCDS - 1) / XCDS, std::max(1, 32 * halo_waves(TM, TN) / ny)) * XCDS;
+    hipLaunchKernelGGL((k_conv3_halo<TM, TN, WX, WY, WN, EP>), dim3((unsigned)groups, ny), dim3(64 * WX * WY * WN), 0, st, x,
+                       wf, K, ep, N, (int)tiles);
     return hipGetLastError();
 }
 
@@ -605,11 +718,25 @@ inline bool halo_ok(const Tens& x, int N) {
     return TW != 0 && x.H % (128 / TW) == 0;
 }
 
+// The workgroup's shape: 256 pixels x 32 or 64 channels, or 128 x 128, in rows of 32
+// pixels (16 where the width has no whole 32); where that leaves fewer than two workgroups a
+// CU, 64 pixels x 64 channels (128 x 32), whose waves have a quarter of the work: at 16 x 16
+// pixels and 512 -> 256 channels 20 us, against 55 for the 128 x 128 tile of the kernel before.
 template <class EP>
 hipError_t conv_halo(const Tens& x, const uint16_t* wf, int K, const EP& ep, int N, int64_t P, hipStream_t st) {
-    if (N <= 32) return conv_halo_bn<32>(x, wf, K, ep, N, P, st);
-    if (N <= 64) return conv_halo_bn<64>(x, wf, K, ep, N, P, st);
-    return conv_halo_bn<128>(x, wf, K, ep, N, P, st);
+    const int64_t groups = P / (N <= 64 ? 256 : 128) * ((N + 127) / 128);
+    if (groups < 512)
+        return N <= 32 ? conv_halo_as<4, 1, 1, 2, 2>(x, wf, K, ep, N, P, st)
+                       : conv_halo_as<4, 1, 1, 1, 4>(x, wf, K, ep, N, P, st);
+    const bool wide = x.W % 32 == 0;
+    if (N <= 32)
+        return wide ? conv_halo_as<4, 2, 2, 2, 1>(x, wf, K, ep, N, P, st)
+                    : conv_halo_as<4, 2, 1, 4, 1>(x, wf, K, ep, N, P, st);
+    if (N <= 64)
+        return wide ? conv_halo_as<4, 4, 2, 2, 1>(x, wf, K, ep, N, P, st)
+                    : conv_halo_as<4, 4, 1, 4, 1>(x, wf, K, ep, N, P, st);
+    return wide ? conv_halo_as<4, 4, 2, 1, 2>(x, wf, K, ep, N, P, st)
+                : conv_halo_as<4, 4, 1, 2, 2>(x, wf, K, ep, N, P, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -946,19 +1073,20 @@ __global__ void k_adam(float* p, float* m1, float* m2, const float* g, int64_t n
 
 // BF16 operand copies of one 3x3 layer's master weights W[co][tap][ci]:
 //   fwd[co][kp], k = tap * ci_n + ci (zero-padded to kp);
-//   dgrad[ci][tap' * co_n + co] = W[co][8 - tap'][ci] (null for the input layer).
-__global__ void k_wconv3(const float* W, int co_n, int ci_n, int kp, uint16_t* fwd, uint16_t* dgrad) {
+//   dgrad[ci][tap' * co_n + co] = W[co][8 - tap'][ci] (null for the input layer);
+// both in fragment order where the channels come in slabs (frag).
+__global__ void k_wconv3(const float* W, int co_n, int ci_n, int kp, int frag, uint16_t* fwd, uint16_t* dgrad) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t nf = (int64_t)co_n * kp;
     if (i < nf) {
         const int co = (int)(i / kp), k = (int)(i - (int64_t)co * kp);
-        fwd[i] = k < 9 * ci_n ? f2bf(W[(int64_t)co * 9 * ci_n + k]) : (uint16_t)0;
+        fwd[frag ? frag_at(co, k, kp) : i] = k < 9 * ci_n ? f2bf(W[(int64_t)co * 9 * ci_n + k]) : (uint16_t)0;
     }
     if (dgrad && i < (int64_t)co_n * 9 * ci_n) {
         const int ci = (int)(i / (9 * co_n));
         const int r = (int)(i - (int64_t)ci * 9 * co_n);
         const int tp = r / co_n, co = r - tp * co_n;
-        dgrad[i] = f2bf(W[((int64_t)co * 9 + (8 - tp)) * ci_n + ci]);
+        dgrad[frag ? frag_at(ci, r, 9 * co_n) : i] = f2bf(W[((int64_t)co * 9 + (8 - tp)) * ci_n + ci]);
     }
 }
 
@@ -993,6 +1121,7 @@ hipError_t conv3_fwd(const Tens& x, const uint16_t* wf, const float* bias, int r
     }
     const int K = 9 * x.C;
     if (halo_ok(x, y.C)) return conv_halo(x, wf, K, ep, y.C, P, st);
+    if (frag_order(x.C, y.C)) return gemm_rows(OpConv3{x, P, K}, OpFrag{wf, y.C, K}, ep, P, y.C, K, st);
     ob.K = K; ob.ld = K;
     return gemm_rows(OpConv3{x, P, K}, ob, ep, P, y.C, K, st);
 }
@@ -1003,6 +1132,7 @@ hipError_t conv3_dgrad(const Tens& g, const uint16_t* wd, const Tens& gx, const 
     EpAct ep{gx.p, gx.ld, gx.off, nullptr, 0, mask ? mask->p : nullptr,
              mask ? mask->ld : 0, mask ? mask->off : 0};
     if (halo_ok(g, gx.C)) return conv_halo(g, wd, K, ep, gx.C, P, st);
+    if (frag_order(g.C, gx.C)) return gemm_rows(OpConv3{g, P, K}, OpFrag{wd, gx.C, K}, ep, P, gx.C, K, st);
     OpPlain ob{wd, (int64_t)gx.C, K, K, 0};
     return gemm_rows(OpConv3{g, P, K}, ob, ep, P, gx.C, K, st);
 }
@@ -1124,7 +1254,8 @@ hipError_t adam(float* p, float* m1, float* m2, const float* g, int64_t n, float
 hipError_t weights_conv3(const float* W, int co_n, int ci_n, uint16_t* fwd, uint16_t* dgrad, hipStream_t st) {
     const int kp = ci_n == 1 ? 16 : 9 * ci_n;
     const int64_t n = (int64_t)co_n * (kp > 9 * ci_n ? kp : 9 * ci_n);
-    hipLaunchKernelGGL(k_wconv3, dim3(nblk(n)), dim3(256), 0, st, W, co_n, ci_n, kp, fwd, dgrad);
+    hipLaunchKernelGGL(k_wconv3, dim3(nblk(n)), dim3(256), 0, st, W, co_n, ci_n, kp, (int)frag_order(ci_n, co_n), fwd,
+                       dgrad);
     return hipGetLastError();
 }
 

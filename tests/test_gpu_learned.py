@@ -129,6 +129,42 @@ def test_unet_forward_matches_oracle(bdc, levels, base, B, H, W):
     net.close()
 
 
+# Small batches run the convolutions in small workgroups, large ones in large: the
+# sums' order per output is the same, so an image's output must not depend on its
+# batch, bit for bit.  Widths in whole tiles of 32, of 16, of 8 and (deeper levels) of
+# none, tiles cut by the frame's edges.
+@pytest.mark.parametrize("levels,base,B,H,W", [(4, 32, 180, 64, 96), (4, 32, 360, 64, 48), (4, 32, 240, 64, 72),
+                                               (3, 64, 300, 32, 40), (2, 64, 200, 16, 32), (3, 32, 500, 36, 44)])
+def test_unet_output_does_not_depend_on_the_batch(bdc, levels, base, B, H, W):
+    say("unet batch L=%d base=%d %dx%dx%d" % (levels, base, B, H, W))
+    rng = np.random.default_rng(17)
+    x = rng.gamma(2.0, 0.5, (B, H, W)).astype(np.float32)
+    net = bdc.UNet(levels, base, max_pixels=B * H * W)
+    net.set_params(f32(_params(levels, base, 5)))
+    out = net.forward(x)
+    for i in (0, B // 2, B - 1):
+        np.testing.assert_array_equal(out[i], net.forward(x[i:i + 1])[0])
+    net.close()
+
+
+def test_unet_gradients_do_not_depend_on_copies(bdc):
+    """The gradient of the mean loss over 256 copies of an image is that of the one (a power of
+    two, so every BF16 value is the same; the FP32 sums' order differs)."""
+    rng = np.random.default_rng(18)
+    levels, base, B, H, W = 4, 32, 256, 64, 96
+    p = f32(_params(levels, base, 6))
+    x = rng.gamma(2.0, 0.5, (1, H, W)).astype(np.float32)
+    tgt = f32(rng.standard_normal((1, H, W, 2)))
+    net = bdc.UNet(levels, base, max_pixels=B * H * W, training=True)
+    net.set_params(p)
+    loss1, g1 = net.gradients(x, tgt)
+    g1 = np.array(g1, np.float64)
+    loss, g = net.gradients(np.repeat(x, B, 0), np.repeat(tgt, B, 0))
+    assert abs(loss - loss1) <= 1e-5 * abs(loss1)
+    assert rel_l2(np.asarray(g, np.float64), g1) < 1e-3
+    net.close()
+
+
 @pytest.mark.parametrize("levels,base,B,H,W", [(3, 8, 2, 16, 16), (3, 32, 2, 32, 32), (4, 32, 2, 64, 64)])
 def test_unet_gradients_match_oracle(bdc, levels, base, B, H, W):
     say("unet gradients L=%d base=%d %dx%dx%d" % (levels, base, B, H, W))
