@@ -92,6 +92,7 @@ hipError_t launch_block_series(const Frame& f, const State& S, int burn_in, cons
                                int phase, int k0, int k1, float* dbg_delta, uint8_t* dbg_acc, hipStream_t st);
 // Block-series scan in nine phases (blocks of one phase three blocks apart: B in
 // [(s - 1)/2, s], s * s <= 1024), one wavefront per block; phase in [0, 9).
+int wave_entries(int s);                       // footprint entries per lane: 2, 4, 6, 7 or 16
 size_t wave_series_lds(int B, int s);
 bool wave_series_fits(int B, int s);
 hipError_t launch_wave_series(const Frame& f, const State& S, int burn_in, int B, int phase, int k0, int k1,
@@ -184,7 +185,7 @@ struct Item {
 
 // BK_WAVE<n>: nine-phase block-series items with up to n footprint entries per lane
 enum BatchKind { BK_FORWARD = 0, BK_SERIES = 1, BK_PHASE = 2, BK_MOMENTS = 3, BK_FINALIZE = 4, BK_WAVE4 = 5,
-                 BK_WAVE8 = 6, BK_WAVE16 = 7, BK_PHASE_EM = 8, BK_MOMENTS_EM = 9, BK_KINDS = 10 };
+                 BK_WAVE7 = 6, BK_WAVE16 = 7, BK_PHASE_EM = 8, BK_MOMENTS_EM = 9, BK_KINDS = 10 };
 hipError_t launch_batch_level(int kind, const TileDesc* tiles, const Item* items, int n_items,
                               const double* inv_tab, size_t lds, hipStream_t st);
 hipError_t launch_batch_advance(int64_t* const* tps, int n, hipStream_t st);

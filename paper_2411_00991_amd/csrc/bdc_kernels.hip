@@ -1532,14 +1532,14 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
             float2 Bq[4];
             float maq[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < 4 && g + u < NQ; ++u) {
                 const int ri = ring_index(g + u);
                 Aq[u] = ring.A[ri];
                 Bq[u] = ring.B[ri];
                 maq[u] = ring.ma[ri];
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < 4 && g + u < NQ; ++u) {
                 const int q = g + u;
                 const float dq = mul_rn(d0, pw[q]), y = fmaf(pw[q], d0, Aq[u].x);
                 Dq[q] = Aq[u].x;
@@ -2855,9 +2855,19 @@ bool block_series_fits(int B, int s) {
     return B <= s && B >= s - 1 && B >= 1 && s * s <= SER_Q * WG && block_series_lds(B, s) <= BLOCK_SERIES_LDS_MAX;
 }
 
+// Entries per lane of the instantiations: whole footprints up to sides 11, 15, 19, 21 and 32
+// (an instantiation's every entry is evaluated).  64^2, Gaussian 11 x 11, 4 chains, 20 sweeps:
+// 50.6 ms with four entries, 45.6 with two; 929 x 914, Airy 19 x 19, 3 sweeps: 11.7 with eight,
+// 11.0 with six.  A batch runs its tiles with 4, 7 or 16: five kinds of pass are five
+// branches of its graph, which took 77.6 ms for 64 tiles where three take 71.1.
+int wave_entries(int s) {
+    const int n = (s * s + 63) / 64;
+    return n <= 2 ? 2 : n <= 4 ? 4 : n <= 6 ? 6 : n <= 7 ? 7 : 16;
+}
+
 size_t wave_series_lds(int B, int s) {
     const int RW = B + 2 * (s / 2);
-    const int cap = ws_cap((s * s + 63) / 64);
+    const int cap = ws_cap(wave_entries(s));
     return (cap + 1) * sizeof(float4) + (cap + 4) * sizeof(int) +
            ((size_t)s * RW + 1) * (sizeof(float4) + sizeof(float2) + sizeof(float));
 }
@@ -2874,17 +2884,18 @@ hipError_t launch_wave_series(const Frame& f, const State& S, int burn_in, int B
     const int nby_p = (nby - py + 2) / 3, nbx_p = (nbx - px + 2) / 3;
     if (nby_p <= 0 || nbx_p <= 0) return hipSuccess;
     const size_t lds = wave_series_lds(B, f.s);
-    const int F = f.s * f.s;
     const dim3 grid = xcd_grid(nby_p * nbx_p, f.C);
-    if (F <= 4 * 64)
-        hipLaunchKernelGGL(k_wave_series<4>, grid, dim3(64), lds, st, f, S, burn_in, B, py, px, k0, k1, dbg_delta,
-                           dbg_acc, nby_p * nbx_p);
-    else if (F <= 8 * 64)
-        hipLaunchKernelGGL(k_wave_series<8>, grid, dim3(64), lds, st, f, S, burn_in, B, py, px, k0, k1, dbg_delta,
-                           dbg_acc, nby_p * nbx_p);
-    else
-        hipLaunchKernelGGL(k_wave_series<16>, grid, dim3(64), lds, st, f, S, burn_in, B, py, px, k0, k1, dbg_delta,
-                           dbg_acc, nby_p * nbx_p);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(64), lds, st, f, S, burn_in, B, py, px, k0, k1, dbg_delta, dbg_acc,
+                           nby_p * nbx_p);
+    };
+    switch (wave_entries(f.s)) {
+        case 2: go(k_wave_series<2>); break;
+        case 4: go(k_wave_series<4>); break;
+        case 6: go(k_wave_series<6>); break;
+        case 7: go(k_wave_series<7>); break;
+        default: go(k_wave_series<16>); break;
+    }
     return hipGetLastError();
 }
 
@@ -3086,7 +3097,7 @@ hipError_t launch_batch_level(int kind, const TileDesc* tiles, const Item* items
         case BK_MOMENTS: hipLaunchKernelGGL(k_batch<BK_MOMENTS>, g, blk, lds, st, tiles, items, inv_tab); break;
         case BK_FINALIZE: hipLaunchKernelGGL(k_batch<BK_FINALIZE>, g, blk, lds, st, tiles, items, inv_tab); break;
         case BK_WAVE4: hipLaunchKernelGGL(k_batch_wave<4>, g, dim3(64), lds, st, tiles, items); break;
-        case BK_WAVE8: hipLaunchKernelGGL(k_batch_wave<8>, g, dim3(64), lds, st, tiles, items); break;
+        case BK_WAVE7: hipLaunchKernelGGL(k_batch_wave<7>, g, dim3(64), lds, st, tiles, items); break;
         case BK_WAVE16: hipLaunchKernelGGL(k_batch_wave<16>, g, dim3(64), lds, st, tiles, items); break;
         case BK_PHASE_EM: hipLaunchKernelGGL(k_batch<BK_PHASE_EM>, g, blk, lds, st, tiles, items, inv_tab); break;
         case BK_MOMENTS_EM:

@@ -1843,7 +1843,7 @@ bdc_status bdc_batch_create(bdc_ctx* const* tiles, int32_t n_tiles, void* hip_st
             b->cmax = std::max(b->cmax, c->C);
             // an EMCCD tile always scans block phases (its contexts refuse the series scans)
             const bool em = c->cfg.camera == BDC_CAMERA_EMCCD;
-            const int pass_kind = T.series == 2 ? (F <= 4 * 64 ? BK_WAVE4 : F <= 8 * 64 ? BK_WAVE8 : BK_WAVE16)
+            const int pass_kind = T.series == 2 ? (F <= 4 * 64 ? BK_WAVE4 : F <= 7 * 64 ? BK_WAVE7 : BK_WAVE16)
                                   : T.series == 1 ? BK_SERIES
                                   : em            ? BK_PHASE_EM
                                                   : BK_PHASE;

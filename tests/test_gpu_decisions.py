@@ -73,6 +73,10 @@ SERIES_CASES = [
     ("SERIES9", 0, ("airy", 21), 80, 60, 1.0, 0.0),
     ("SERIES9", 0, ("airy", 31), 64, 70, 1.0, 0.15),
     ("SERIES9", 0, ("gauss", 3), 19, 26, 2.0, 0.0),
+    ("SERIES9", 0, ("gauss", 13), 40, 45, 1.0, 0.0),         # either side of 4, 6 and 7 entries per lane
+    ("SERIES9", 0, ("gauss", 17), 50, 41, 5.0, 0.0),
+    ("SERIES9", 0, ("airy", 19), 57, 60, 1.0, 0.0),
+    ("SERIES9", 0, ("gauss", 23), 60, 52, 1.0, 0.0),
 ]
 
 
