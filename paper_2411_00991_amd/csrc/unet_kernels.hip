@@ -740,6 +740,78 @@ hipError_t conv_halo(const Tens& x, const uint16_t* wf, int K, const EP& ep, int
 }
 
 // ---------------------------------------------------------------------------
+// Transposed 2x2 stride-2 convolution, channels in slabs of 32: a wave owns 16 TM
+// low-resolution pixels x 64 of the 4 C outputs n = (i, j, c), takes its operands (weights
+// in fragment order as the MFMA's rows, pixels as its columns) straight from memory one
+// slab ahead, and stores each lane's eight channels of a child pixel.  No LDS, no barrier.
+// What bounds it: the stores, half lines of the concatenation it writes into, and at
+// 16 x 16 pixels the latency of its slabs.  Forward at 2048^2, by level, against the 128 x
+// 128 tile of k_gemm: 99, 157, 286 -> 65, 82, 154 us; at 128^2 22, 18, 17 -> 5, 4, 4 us.
+// ---------------------------------------------------------------------------
+template <int TM>
+__global__ void __launch_bounds__(NT) k_up(OpPlain x, OpFrag w, EpUp ep) {
+    constexpr int TN = 4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, r16 = lane & 15;
+    const int64_t m0 = ((int64_t)blockIdx.x * (NT / 64) + wave) * (16 * TM);
+    if (m0 >= x.M) return;
+    const int nf0 = blockIdx.y * TN, nk = x.K / 32;
+    const uint16_t* px[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int64_t m = m0 + i * 16 + r16;
+        px[i] = x.p + (m < x.M ? m : x.M - 1) * x.ld + x.off + g * 8;
+    }
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    bf16x8 fx[2][TM], fw[2][TN];
+    auto fetch = [&](int set, int k) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fw[set][j] = w.frag(nf0 + j, k, lane);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fx[set][i] = *(const bf16x8*)(px[i] + k * 32);
+    };
+    auto step = [&](int set, int k) {
+        if (k + 1 < nk) fetch(set ^ 1, k + 1);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[set][j], fx[set][i], acc[i][j], 0, 0, 0);
+    };
+    fetch(0, 0);
+    for (int k = 0; k < nk; k += 2) {
+        step(0, k);
+        if (k + 1 < nk) step(1, k + 1);
+    }
+    const Tens& t = ep.t;
+#pragma unroll
+    for (int j = 0; j < TN; j += 2) {
+        const int n = ((nf0 + j) >> 1) * 32 + g * 8, ij = n / t.C, c = n - ij * t.C;
+        float bv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bv[e] = ep.bias[c + e];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int64_t m = m0 + i * 16 + r16;
+            if (m >= x.M) continue;
+            int b, y, xx;
+            pixel_of(m, ep.Hl, ep.Wl, b, y, xx);
+            uint32_t v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const f32x4& d = acc[i][j + e / 2];
+                v[e] = bf2(d[2 * (e & 1)] + bv[2 * e], d[2 * (e & 1) + 1] + bv[2 * e + 1]);
+            }
+            const int64_t q = ((int64_t)b * t.H + 2 * y + (ij >> 1)) * t.W + 2 * xx + (ij & 1);
+            *(uint4*)(t.p + q * t.ld + t.off + c) = make_uint4(v[0], v[1], v[2], v[3]);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Small kernels
 // ---------------------------------------------------------------------------
 // Sum of split-K partials into FP32 gradient entries: out[base + m * ms + n * ns] = sum_z part[z][m][n].
@@ -1163,13 +1235,13 @@ __global__ void k_wconv3(const float* W, int co_n, int ci_n, int kp, int frag, u
     }
 }
 
-// Transposed 2x2 layer, master Wt[ij][co][ci]: fwd = same order;
-// dgrad[ci][ij * co_n + co].
-__global__ void k_wup(const float* W, int co_n, int ci_n, uint16_t* fwd, uint16_t* dgrad) {
+// Transposed 2x2 layer, master Wt[ij][co][ci]: fwd = same order, or the fragment order of
+// its 4 co_n rows of ci_n (frag); dgrad[ci][ij * co_n + co].
+__global__ void k_wup(const float* W, int co_n, int ci_n, int frag, uint16_t* fwd, uint16_t* dgrad) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t n = (int64_t)4 * co_n * ci_n;
     if (i >= n) return;
-    fwd[i] = f2bf(W[i]);
+    fwd[frag ? frag_at((int)(i / ci_n), (int)(i % ci_n), ci_n) : i] = f2bf(W[i]);
     const int ci = (int)(i / (4 * co_n));
     const int r = (int)(i - (int64_t)ci * 4 * co_n);          // ij * co_n + co
     dgrad[i] = f2bf(W[(int64_t)r * ci_n + ci]);
@@ -1237,6 +1309,15 @@ hipError_t up_fwd(const Tens& x, const uint16_t* wf, const float* bias, const Te
                   hipStream_t st) {
     EpUp ep{y, Hl, Wl, bias};
     OpPlain oa{x.p, P_lo, x.C, x.ld, x.off};
+    if (frag_order(x.C, y.C)) {
+        // 64 pixels a wave; 16 where that leaves fewer than two workgroups a CU (and the
+        // slabs' latency counts, not the weights' reuse)
+        const bool small = P_lo / 256 * (y.C / 16) < 512;
+        const dim3 grid(nblk(P_lo, small ? 64 : 256), (unsigned)(y.C / 16));
+        if (small) hipLaunchKernelGGL(k_up<1>, grid, dim3(NT), 0, st, oa, OpFrag{wf, 4 * y.C, x.C}, ep);
+        else hipLaunchKernelGGL(k_up<4>, grid, dim3(NT), 0, st, oa, OpFrag{wf, 4 * y.C, x.C}, ep);
+        return hipGetLastError();
+    }
     OpPlain ob{wf, (int64_t)4 * y.C, x.C, x.C, 0};
     return gemm_rows(oa, ob, ep, P_lo, 4 * y.C, x.C, st);
 }
@@ -1335,7 +1416,8 @@ hipError_t weights_conv3(const float* W, int co_n, int ci_n, uint16_t* fwd, uint
 }
 
 hipError_t weights_up(const float* W, int co_n, int ci_n, uint16_t* fwd, uint16_t* dgrad, hipStream_t st) {
-    hipLaunchKernelGGL(k_wup, dim3(nblk((int64_t)4 * co_n * ci_n)), dim3(256), 0, st, W, co_n, ci_n, fwd, dgrad);
+    hipLaunchKernelGGL(k_wup, dim3(nblk((int64_t)4 * co_n * ci_n)), dim3(256), 0, st, W, co_n, ci_n, (int)frag_order(ci_n, co_n), fwd,
+                       dgrad);
     return hipGetLastError();
 }
 
