@@ -2,7 +2,9 @@
 // the learned warm start and the block independence proposal.
 //
 // Every convolution is one implicit GEMM, C[m][n] = sum_k A[m][k] B[n][k], on
-// the gfx950 16x16x32 BF16 MFMA with FP32 accumulation.  A workgroup of four
+// the gfx950 16x16x32 BF16 MFMA with FP32 accumulation.  Layers whose channels
+// come in slabs of 32 run k_conv3_halo (3x3, whole tiles) and k_up (transposed); the
+// others, and all weight gradients, k_gemm: a workgroup of four
 // waves owns a BM x BN tile (waves 2 x 2), stages 32-wide K slices of A and B
 // in LDS (double-buffered, rows K-contiguous), and the operand policies below
 // generate the addresses of the convolution being computed:
