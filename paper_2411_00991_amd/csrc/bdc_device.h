@@ -131,6 +131,19 @@ __device__ inline double exp_small(float y) {
     return (double)__builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
 }
 
+// The 2a that a pixel's record holds.  The recurrences step by exp_small(2a), whose
+// rounding is another 2a, off by up to 6e-8: over a window of n terms that moves a
+// mean count's change by up to n 6e-8 of it, and by another amount in another window.
+// Below WIDE_A2 (read noise above ten photons, windows of hundreds of terms) the
+// record therefore holds the logarithm of that step, so that every evaluation of the
+// pixel agrees on its read noise, which is off by 3e-6 of itself at 10 photons and by
+// 3e-4 at 100.
+constexpr float WIDE_A2 = 0.01f;
+__device__ inline float record_a2(float a2) {
+    const double q = exp_small(a2);
+    return a2 < WIDE_A2 && q > 1.0 ? (float)log(q) : a2;
+}
+
 // 1/n, 1/(n-1), 1/(n-2), 1/(n-3) for 4 <= n < 2^20 from one hardware
 // reciprocal of their product and one Newton step: each reciprocal is the
 // product of the other three factors with it (relative error below 1e-15).
@@ -246,10 +259,10 @@ __device__ inline double lgamma_diff(int k, int k0) {   // lgamma(k+1) - lgamma(
     return s;
 }
 
-__device__ __noinline__ double delta_ell_sharp(float d, float lmu, float lx, Window win, PixConst pc) {
-    int k0 = (int)rintf(fmaxf(pc.c, 0.0f));
+__device__ inline double delta_ell_sharp(float d, float lmu, float lx, Window win, float cf, float a2) {
+    int k0 = (int)rintf(fmaxf(cf, 0.0f));
     k0 = k0 < win.lo ? win.lo : (k0 > win.hi ? win.hi : k0);
-    const double a = 0.5 * (double)pc.a2, c = pc.c, lmd = (double)lmu;
+    const double a = 0.5 * (double)a2, c = cf, lmd = (double)lmu;
     double s0 = 0.0, s1 = 0.0;
     for (int k = win.lo; k <= win.hi; ++k) {
         const double lw = -a * ((k - c) * (k - c) - (k0 - c) * (k0 - c)) + (k - k0) * lmd - lgamma_diff(k, k0);
@@ -257,6 +270,48 @@ __device__ __noinline__ double delta_ell_sharp(float d, float lmu, float lx, Win
         s1 += exp_wide(lw + (k - k0) * (double)lx);
     }
     return -(double)d + (double)k0 * (double)lx + log_ratio(s1, s0);
+}
+
+// ---------------------------------------------------------------------------
+// Long windows.  The sums of the recurrences below are relative to the window's
+// lowest weight, which a mode hundreds of counts above it takes out of the double
+// range (a = 0.00317, c = 482, mu 480 -> 11: the value is -595, an overflowed sum gave
+// +359).  Windows of more than LONG_WINDOW terms and sums beyond SUM_MAX are taken
+// here, with sums scaled down as they grow and, since they are long, exp(2a) in double.
+// ---------------------------------------------------------------------------
+constexpr int LONG_WINDOW = 128;
+constexpr double SUM_MAX = 1e300;
+
+// log(sum_k W_k x^k / sum_k W_k) - d over the window.
+__device__ inline double delta_ell_long(float mu, float d, Window win, float c, float a2) {
+    const double m = (double)mu, x = 1.0 + (double)d / m, qi = exp((double)a2);
+    double G = m * exp(-(double)a2 * ((double)win.hi - 0.5 - (double)c));
+    double acc0 = 0.0, acc1 = 0.0, one0 = 1.0, one1 = 1.0;          // sums and the lowest weight, times 2^-e
+    int e = 0;                                                      // e1 - e0
+#pragma unroll 1
+    for (int n = win.hi; n > win.lo; --n) {
+        const double r = G * rcp_nr2((double)n);
+        G *= qi;
+        acc0 = r * (acc0 + one0);
+        acc1 = r * x * (acc1 + one1);
+        if (acc0 > 0x1p500) {
+            acc0 *= 0x1p-500;
+            one0 *= 0x1p-500;
+            e -= 500;
+        }
+        if (acc1 > 0x1p500) {
+            acc1 *= 0x1p-500;
+            one1 *= 0x1p-500;
+            e += 500;
+        }
+    }
+    return log((one1 + acc1) / (one0 + acc0)) + (double)e * 0.69314718055994531 + (double)win.lo * log(x) - (double)d;
+}
+
+// What the recurrences do not take.  (One call for all: a call site costs its kernel
+// registers.)
+__device__ __noinline__ double delta_ell_rare(float mu, float d, float lmu, float lx, Window win, float c, float a2) {
+    return a2 > 2.0f * A_RECUR_MAX ? delta_ell_sharp(d, lmu, lx, win, c, a2) : delta_ell_long(mu, d, win, c, a2);
 }
 
 // ---------------------------------------------------------------------------
@@ -294,8 +349,9 @@ __device__ inline Series series_of_log(double g1, double g2, double g3, double g
     const double im = rcp_nr2((double)mu), im2 = im * im;
     out.b = make_float4((float)(g1 * im - 1.0), (float)(g2 * im2), (float)(g3 * im2 * im), (float)(g4 * im2 * im2));
     // radius: u0 = (tau/2 * 5 / s2)^(1/5) solves s2 u^5 / 5 = tau/2; the factor
-    // (1 - u0)^(1/5) makes room for the 1/(1 - u) of the bound
-    const float s2v = fmaxf((float)(-2.0 * g2), 1e-30f);
+    // (1 - u0)^(1/5) makes room for the 1/(1 - u) of the bound; R = 0 where a sum
+    // overflowed and the coefficients are no numbers
+    const float s2 = (float)(-2.0 * g2), s2v = s2 == s2 ? fmaxf(s2, 1e-30f) : INFINITY;
     float u = __builtin_amdgcn_exp2f(0.2f * __builtin_amdgcn_logf(2.5f * SERIES_TAU * __builtin_amdgcn_rcpf(s2v)));
     u = fminf(u, 0.5f);
     u *= __builtin_amdgcn_exp2f(0.2f * __builtin_amdgcn_logf(1.0f - u));
@@ -442,10 +498,10 @@ __device__ inline double delta_ell_emccd(float mu, float d, const PixConst& pc) 
 // the window's lower end, so x^k -> x^(k - lo)), in double precision:
 //   acc0 <- r_k (1 + acc0),  acc1 <- x r_k (1 + acc1),  r_k = G_k / (k + 1),
 //   G_k = mu exp(-a(2k + 1 - 2c)),  G_{k-1} = G_k exp(2a).
-// For a <= A_RECUR_MAX the window's summands span far less than the double
-// range (TAIL_T nats deep plus a bracket of a few photons), so the
-// normalisation at lo cannot overflow.  Returns NaN when mu + d <= 0 or on
-// overflow (the caller then rejects).  inv_tab[k] = 1/k for k < INV_TABLE.
+// For a <= A_RECUR_MAX and a short window the summands span less than the double
+// range (TAIL_T nats deep plus a bracket of a few photons); delta_ell_rare takes the
+// others.  Returns NaN when mu + d <= 0 and for counts beyond the window's range
+// (the caller then rejects).  inv_tab[k] = 1/k for k < INV_TABLE.
 // ---------------------------------------------------------------------------
 // TABLE: 1/(k+1) from inv_tab (staged in LDS by the caller), else computed
 // (recip4), which keeps memory latency out of the recurrence when no table
@@ -461,7 +517,6 @@ __device__ inline double delta_ell_t(float mu, float d, const PixConst& pc, cons
     const Window win = phi_window(lmu + fminf(lx, 0.0f), lmu + fmaxf(lx, 0.0f), pc);
     if (!win.ok) return __builtin_nan("");
     nterms += win.hi - win.lo + 1;                // the window's terms (work measure)
-    if (pc.a2 > 2.0f * A_RECUR_MAX) return delta_ell_sharp(d, lmu, lx, win, pc);
     // The recurrence runs in steps of four terms: the window is widened to a
     // multiple of four (downwards while that stays >= 0, else upwards).  Extra
     // summands only add more of the exact sum.
@@ -475,7 +530,9 @@ __device__ inline double delta_ell_t(float mu, float d, const PixConst& pc, cons
     // |exponent| <= 2 A_RECUR_MAX (2^20 + 1): within exp_wide_b's range
     double G = (double)mu * exp_wide_b(-(double)pc.a2 * ((double)k_top + 0.5 - (double)pc.c));
     double acc0 = 0.0, acc1 = 0.0;
-    if (!TABLE || hi < INV_TABLE) {
+    const bool rare = pc.a2 > 2.0f * A_RECUR_MAX || win.hi - win.lo > LONG_WINDOW;
+    if (rare) {
+    } else if (!TABLE || hi < INV_TABLE) {
         const double* iv = inv_tab + hi;          // iv[-i] = 1 / (hi - i)
 #pragma unroll 1
         for (int i = 0; i < n4; i += 4) {
@@ -507,6 +564,7 @@ __device__ inline double delta_ell_t(float mu, float d, const PixConst& pc, cons
     }
     // log((1 + acc1)/(1 + acc0)): the sums are normalised at the window's low
     // end and may exceed the FP32 range, so the ratio stays in double.
+    if (rare || !(acc0 < SUM_MAX && acc1 < SUM_MAX)) return delta_ell_rare(mu, d, lmu, lx, win, pc.c, pc.a2);
     return fma((double)lo, (double)lx, log_ratio(1.0 + acc1, 1.0 + acc0) - (double)d);
 }
 
@@ -515,7 +573,7 @@ __device__ inline double delta_ell(float mu, float d, const PixConst& pc, const 
 }
 
 // The same without a reciprocal table.
-__device__ inline double delta_ell_notab(float mu, float d, const PixConst& pc, int& nterms) {
+__device__ __noinline__ double delta_ell_notab(float mu, float d, const PixConst& pc, int& nterms) {
     return delta_ell_t<false>(mu, d, pc, nullptr, nterms);
 }
 
@@ -545,7 +603,7 @@ struct DirectWindow {
     int lo, hi, n;     // window [lo, hi), widened to a multiple of four terms
     int terms;         // the window's terms (work measure)
     int kind;          // 0: the recurrence, 1: no value (the caller rejects), 2: sharp read noise
-    Window win;        // the window before widening (kind 2)
+    Window win;        // the window before widening
     float lmu;
 };
 
@@ -577,12 +635,13 @@ __device__ inline DirectWindow direct_window(float mu, float d, const PixConst& 
     return w;
 }
 
-__device__ inline double delta_ell_direct(float mu, float d, const PixConst& pc, int& nterms) {
+// (Calls: few updates come here, and inlined they would take the scans' registers.)
+__device__ __noinline__ double delta_ell_direct(float mu, float d, const PixConst& pc, int& nterms) {
     if (d == 0.0f && mu > 0.0f) return 0.0;
     const DirectWindow w = direct_window(mu, d, pc);
     nterms += w.terms;
     if (w.kind == 1) return __builtin_nan("");
-    if (w.kind == 2) return delta_ell_sharp(d, w.lmu, w.lx, w.win, pc);
+    const bool rare = w.kind == 2 || w.win.hi - w.win.lo > LONG_WINDOW;
     // Four Horner steps acc <- (G_u / n_u)(1 + acc) at a time (n_u = hi - i - u,
     // G_u = G qi^u) over their common denominator N = n0 n1 n2 n3:
     //   acc <- G3 [n2 n1 n0 + G2 (n1 n0 + G1 (n0 + G0 (1 + acc)))] / N,
@@ -591,7 +650,7 @@ __device__ inline double delta_ell_direct(float mu, float d, const PixConst& pc,
     // recurrence.
     double G = w.G, acc0 = 0.0, acc1 = 0.0;
 #pragma unroll 1
-    for (int i = 0; i < w.n; i += 4) {
+    for (int i = 0; i < (rare ? 0 : w.n); i += 4) {
         const double n0 = (double)(w.hi - i), n1 = n0 - 1.0, n2 = n0 - 2.0, n3 = n0 - 3.0;   // n3 >= lo + 1 >= 1
         const double p10 = n1 * n0, p210 = n2 * p10, N = n3 * p210;
         double iN = __builtin_amdgcn_rcp(N);
@@ -608,6 +667,7 @@ __device__ inline double delta_ell_direct(float mu, float d, const PixConst& pc,
         t = fma(x2, t, p210);
         acc1 = (x3 * t) * iN;
     }
+    if (rare || !(acc0 < SUM_MAX && acc1 < SUM_MAX)) return delta_ell_rare(mu, d, w.lmu, w.lx, w.win, pc.c, pc.a2);
     return fma((double)w.lo, (double)w.lx, log_ratio(1.0 + acc1, 1.0 + acc0) - (double)d);
 }
 

@@ -177,7 +177,7 @@ __global__ void k_pixel_consts(Frame f, float4* pc, int* bad) {
     }
     const double a = (double)G * (double)G / (2.0 * (double)sg * (double)sg);
     const PixConst p = make_pc(c, a);
-    pc[n] = make_float4(p.c, p.a2, p.L0, p.iB);
+    pc[n] = make_float4(p.c, record_a2(p.a2), p.L0, p.iB);
 }
 
 __global__ void k_init_state(Frame f, State S, const float* rho0, float log_step0, int* bad) {

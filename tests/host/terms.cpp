@@ -1,0 +1,39 @@
+// The likelihood terms of bdc_device.h on the host, for test_term_bounds.py.
+#include "builtins.h"
+
+#include "bdc_device.h"
+
+using namespace bdc;
+
+// Per-pixel constants as the frame set-up stores them and the kernels load them.
+static PixConst make_pc(double c, double a) {
+    PixConst p;
+    const double ks = c > 0.0 ? c : 0.0;
+    p.c = (float)c;
+    p.a2 = record_a2((float)(2.0 * a));
+    p.ks = fmaxf(p.c, 0.0f);
+    p.L0 = (float)(2.0 * a * (c - ks) - std::log(ks + 1.0));
+    p.iB = (float)(1.0 / (2.0 * a + 1.0 / (ks + 1.0)));
+    p.inv2a = 1.0f / p.a2;
+    p.h0 = std::sqrt(2.0f * TAIL_T * p.inv2a);
+    return p;
+}
+
+extern "C" {
+
+// The two direct evaluations; a2: in, and as the record holds it; longer: whether the
+// window counts as long.
+void direct(int n, const float* c, const float* a2, const float* mu, const float* d, float* held, double* out, double* out2,
+            int* longer) {
+    for (int i = 0; i < n; ++i) {
+        const PixConst pc = make_pc(c[i], 0.5 * (double)a2[i]);
+        int terms = 0;
+        held[i] = pc.a2;
+        out[i] = delta_ell_direct(mu[i], d[i], pc, terms);
+        out2[i] = delta_ell_notab(mu[i], d[i], pc, terms);
+        const Window w = direct_window(mu[i], d[i], pc).win;
+        longer[i] = w.hi - w.lo > LONG_WINDOW;
+    }
+}
+
+}  // extern "C"
