@@ -2052,7 +2052,7 @@ __device__ void bounded_block(const Frame& f, const State& S, int burn_in, const
                 const bool out = valid && !want_delta && !(fabsf(y) <= A.y);
                 const float ym = out ? fabsf(D) : fmaxf(fabsf(y), fabsf(D)), y2 = ym * ym;
                 const float trunc = fabsf(b.w) * (y2 * y2) * (3.2f * ym * fast_rcp(A.x));
-                float c = d * series_slope(b, D, y), e = 4e-6f * cnt * fabsf(d);
+                float c = d * series_slope(b, D, y), e = BND_REL * cnt * fabsf(d);
                 if (out) {
                     const TermBound tb = series_bound(A.x, b, D, y, c);
                     c = tb.c;

@@ -36,4 +36,31 @@ void direct(int n, const float* c, const float* a2, const float* mu, const float
     }
 }
 
+// Interval and direct evaluation of moves mu -> mu + d, mu = m + shift R, of a pixel whose
+// series was formed at m = m0 + dm: over the window of that move, or (m0 = 0) over its
+// own.  radius: R, -1 where no series was formed.
+void bounds(int n, const float* c, const float* a2, const float* m0, const float* dm, const float* shift, const float* step,
+            double* centre, double* half, double* value, double* radius) {
+    for (int i = 0; i < n; ++i) {
+        const PixConst pc = make_pc(c[i], 0.5 * (double)a2[i]);
+        int terms = 0;
+        const float m = m0[i] + dm[i];
+        Series s;
+        if (m0[i] > 0.0f) {
+            quad.run([&](int lane) {
+                Series one = series_after(m0[i], dm[i], pc, lane, terms);
+                if (lane == 0) s = one;
+            }, 4);
+        } else {
+            s = series_at(m, pc, terms);
+        }
+        const float mu = m + shift[i] * s.R, d = mu * step[i], D = mu - m, y = D + d;
+        const TermBound t = series_bound(m, s.b, D, y, series_delta(s.b, D, d));
+        centre[i] = t.c;
+        half[i] = t.e;
+        value[i] = delta_ell_direct(mu, d, pc, terms);
+        radius[i] = s.b.y <= 0.0f ? (fabsf(y) <= s.R ? 0.0 : (double)s.R) : -1.0;
+    }
+}
+
 }  // extern "C"

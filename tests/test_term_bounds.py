@@ -91,3 +91,28 @@ def test_sums_that_overflow_in_short_windows(terms):
         tol = 1e-4 + (c[i] + 200.0) * (3e-7 / max(x, 1e-9) + 1e-5)
         assert abs(out[i] - ref) <= tol, (c[i], a2[i], mu[i], d[i], out[i], ref)
         assert abs(out2[i] - ref) <= tol, (c[i], a2[i], mu[i], d[i], out2[i], ref)
+
+
+@pytest.mark.parametrize("noise", [(0.05, 0.5), (0.5, 2.0), (2.0, 5.0), (5.0, 10.0), (10.0, 20.0), (20.0, 100.0)],
+                         ids=lambda v: "%gto%g" % v)
+def test_intervals_hold_the_direct_evaluation(terms, noise):
+    """What a scan decides from: the direct evaluation lies within 1.02 half-widths and 1e-7 of the
+    centre, at any read noise, anchored at a mean of its own or after a move by up to a factor of
+    e^6 up and 1/100 down, for moves by factors of e^-4 to e^6."""
+    rng = np.random.default_rng(int(noise[0] * 100))
+    n = 120000
+    sg = np.exp(rng.uniform(np.log(noise[0]), np.log(noise[1]), n))
+    true = np.exp(rng.uniform(np.log(0.05), np.log(3000.0), n))
+    c = np.float32(rng.poisson(true) + sg * rng.standard_normal(n))
+    m = np.float32(true * np.exp(rng.normal(0.0, 0.7, n)))
+    last = np.clip(rng.normal(0.0, 1.0, n) * np.where(rng.random(n) < 0.5, 0.3, 2.0), -6.0, 4.6)
+    m0 = np.where(rng.random(n) < 0.4, np.float32(0.0), np.float32(m * np.exp(last)))
+    dm = np.float32(m - m0)
+    shift = np.where(rng.random(n) < 0.3, 0.0, rng.uniform(-1.0, 1.0, n))
+    step = np.expm1(np.clip(rng.normal(0.0, 1.0, n) * np.where(rng.random(n) < 0.6, 0.5, 2.0), -4.0, 6.0))
+    centre, half, value, radius = call(terms.bounds, n, [c, np.float32(1.0 / sg ** 2), m0, dm, shift, step], [np.float64] * 4)
+    tell = (radius > 0.0) & np.isfinite(half) & np.isfinite(centre)
+    assert tell.mean() > 0.3
+    excess = np.abs(value - centre) - (1.02 * half + 1e-7)
+    assert np.isfinite(value[tell]).all()
+    assert excess[tell].max() <= 0.0, (excess[tell].max(), np.flatnonzero(tell)[excess[tell].argmax()])
