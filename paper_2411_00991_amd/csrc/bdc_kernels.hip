@@ -6,6 +6,7 @@
 // batched R-hat statistics, per-chain log-posterior partials) -> finalize
 // (deterministic reduction of the log-posterior, sweep index + 1).
 // The sweep index lives in device memory so a captured sweep replays as is.
+#include "bdc_bounds.h"
 #include "bdc_conv.h"
 #include "bdc_device.h"
 #include "bdc_kernels.h"
@@ -1718,7 +1719,8 @@ __global__ void __launch_bounds__(64) k_wave_series(Frame f, State S, int burn_i
 // sqrt(mu c)), whose zeros in mu are real and not positive, so that log f is a
 // sum of log(1 + beta v) and has the bounds of the sCMOS log-likelihood.  With
 // w = B f / (A + B f) at the anchor and g the change of log f from there, that
-// of log(A + B f) is log(1 + w (e^g - 1)), whose slope in g lies in [0, 1].
+// of log(A + B f) is log(1 + w (e^g - 1)), whose slope in g lies in [0, 1]
+// (bdc_bounds.h).
 //
 // Chunk prior: F_-k = conj F_k for a real object, so a thread holds one frequency
 // of each such pair, its sums in FP32 with their rounding in the bound; the
@@ -1733,68 +1735,9 @@ __global__ void __launch_bounds__(64) k_wave_series(Frame f, State S, int burn_i
 // of a block; four wavefronts of two terms a lane: 5.8 ms); chunk prior 512^2, 31 x 31:
 // 68.5 -> 12.9 ms; 512^2 at k = 2, PSF 63 x 63: 285 -> 58 ms.
 // ---------------------------------------------------------------------------
-constexpr float BND_R = 6.0f;
 constexpr float BND_FLAT = 1e-7f;             // of a term: the direct evaluation's absolute rounding
 constexpr size_t BND_LDS_MAX = 160 * 1024;
 constexpr int BND_MAX_F = 3 * 512;            // footprint entries (three per thread of eight waves)
-
-// Series of log f and the share w of B f of an EMCCD pixel at mean mu.
-struct EmSeries { Series s; float w; };
-
-__device__ __noinline__ EmSeries emccd_series(float muf, float cf, float lA, float lB) {
-    EmSeries o;
-    o.s.R = 0.0f;
-    o.s.b = no_series();
-    o.w = 1.0f;
-    if (!(muf > 0.0f)) return o;
-    if (!(cf > 0.0f)) {                                             // no photon amplified: exactly -mu
-        o.s.b = make_float4(-1.0f, 0.0f, 0.0f, 0.0f);
-        o.s.R = muf;
-        return o;
-    }
-    const double mu = (double)muf, c = (double)cf, q = mu * c, z = 2.0 * sqrt(q);
-    double lf;
-    if (z < 16.0) {
-        // t_k = q^k / (k! (k + 1)!):  sum t_k = 2 I_1 / z, sum (k + 1) t_k = I_0;
-        // mu f' / f = their ratio E, mu^2 f'' = q f
-        double t = 1.0, s0 = 1.0, s1 = 1.0;
-#pragma unroll 4
-        for (int k = 1; k < 64; ++k) {
-            t *= q * rcp_nr((double)(k * (k + 1)));
-            s1 += t;
-            s0 = fma((double)(k + 1), t, s0);
-            if (t < 1e-13 * s1) break;
-        }
-        const double E = s0 * rcp_nr2(s1);
-        lf = (double)fast_ln((float)(mu * s1));
-        o.s = series_finish(1.0, E, 0.5 * q, q * (E - 1.0) * (1.0 / 6.0), q * (q - 2.0 * E + 2.0) * (1.0 / 24.0), 0,
-                            muf);
-    } else {
-        // log f = log(mu / c) / 2 + z - log(2 pi z) / 2 + l(z), z ~ (1 + v)^(1/2) and
-        // l = -3/8 / z - 3/16 / z^2 - 21/128 / z^3 - 0.2109 / z^4 (Hankel's series)
-        const float zf = (float)z, i1 = fast_rcp(zf), l1 = -0.375f * i1, l2 = -0.1875f * i1 * i1,
-                    l3 = -0.1640625f * i1 * i1 * i1, l4 = -0.2109f * i1 * i1 * i1 * i1;
-        const float g1 = 0.5f * zf + 0.25f - 0.5f * l1 - l2 - 1.5f * l3 - 2.0f * l4;
-        const float g2 = -0.125f * zf - 0.125f + 0.375f * l1 + l2 + 1.875f * l3 + 3.0f * l4;
-        const float g3 = 0.0625f * zf + 0.083333333f - 0.3125f * l1 - l2 - 2.1875f * l3 - 4.0f * l4;
-        const float g4 = -0.0390625f * zf - 0.0625f + 0.2734375f * l1 + l2 + 2.4609375f * l3 + 5.0f * l4;
-        lf = (double)(0.5f * (fast_ln(muf * fast_rcp(cf)) - fast_ln(6.2831853f * zf)) + (l1 + l2 + l3 + l4)) + z;
-        o.s = series_of_log(g1, g2, g3, g4, muf);
-    }
-    const float lam = (float)((double)lB + lf - (double)lA);         // log(B f / A)
-    if (lam < 30.0f) o.w = fast_rcp(1.0f + __builtin_amdgcn_exp2f(-1.44269504f * lam));
-    if (!(o.s.b.y <= 0.0f)) {
-        o.s.b = no_series();
-        o.s.R = 0.0f;
-    }
-    return o;
-}
-
-// log(1 + w (e^g - 1)), 0 <= w <= 1, and the argument of the logarithm.
-__device__ inline float em_mix(float w, float g, float& arg) {
-    arg = fmaf(w, __builtin_amdgcn_exp2f(g * 1.44269504f) - 1.0f, 1.0f);
-    return fast_ln(arg);
-}
 
 struct BoundedLds {
     double *red, *red2;                          // [waves]: direct sums; the prior's exact S' - S
@@ -1803,7 +1746,7 @@ struct BoundedLds {
     float4* A;                                   // [RW * RW + 1]: anchor mean, reach of its series, b1, b2
     float2* B;                                   // b3, b4
     float* mu;                                   // current mean, -1 outside the frame
-    float* w;                                    // EMCCD: share of B f
+    float* w;                                    // EMCCD: share of B f, or log(B f / A)
     uint16_t* job;                               // [F]: queued pixels, region index
     float* job_mu;                               // [F]: their means after the move
     double2 *th, *tw;                            // chunk prior: (cos, sin)(2 pi j / n), j < th, j < tw
@@ -1918,7 +1861,7 @@ __device__ void bounded_block(const Frame& f, const State& S, int burn_in, const
         float mu = -1.0f;
         l.A[i] = make_float4(0.0f, -1.0f, 0.0f, 0.0f);
         l.B[i] = make_float2(0.0f, 0.0f);
-        if (EM) l.w[i] = 1.0f;
+        if (EM) l.w[i] = INFINITY;
         if (i < NR && yy >= 0 && yy < f.Hp && xx >= 0 && xx < f.Wp) {
             mu = S.mu[pbase + (int64_t)yy * f.Wp + xx];
             if (!want_delta) {
@@ -2043,40 +1986,16 @@ __device__ void bounded_block(const Frame& f, const State& S, int burn_in, const
                 mq[q] = l.mu[i];
                 const float4 A = l.A[i];
                 const float2 Bv = l.B[i];
-                const float share = EM ? l.w[i] : 1.0f;
-                const float4 b = make_float4(A.z, A.w, Bv.x, Bv.y);
+                const float share = EM ? l.w[i] : 0.0f;
                 const bool valid = mq[q] >= 0.0f;
                 nevals += valid ? 1 : 0;
-                const float d = mul_rn(d0, pw[q]), D = mq[q] - A.x, y = D + d;
-                const float cnt = fabsf(b.x) + 1.0f;
-                const bool out = valid && !want_delta && !(fabsf(y) <= A.y);
-                const float ym = out ? fabsf(D) : fmaxf(fabsf(y), fabsf(D)), y2 = ym * ym;
-                const float trunc = fabsf(b.w) * (y2 * y2) * (3.2f * ym * fast_rcp(A.x));
-                float c = d * series_slope(b, D, y), e = BND_REL * cnt * fabsf(d);
-                if (out) {
-                    const TermBound tb = series_bound(A.x, b, D, y, c);
-                    c = tb.c;
-                    e = tb.e;
-                }
-                if (EM) {
-                    const float gD = fmaf(D, series_slope(b, 0.0f, D), D), gy = gD + c + d;
-                    if (share < 1.0f) {
-                        float ay, aD;
-                        const float my = em_mix(share, gy, ay), mD = em_mix(share, gD, aD);
-                        c = my - mD - d;
-                        // rounding of the share, exponentials, arguments and logarithms
-                        e += fmaf(5e-7f, fabsf(gy) + fabsf(gD), 5e-6f) + 5e-7f * fast_rcp(fminf(ay, aD)) +
-                             4e-6f * cnt * fabsf(D);
-                        if (!(gy < 60.0f && ay > 0.0f && aD > 0.0f)) e = INFINITY;
-                    } else if (!(gy > -12.0f) && b.x != -1.0f) {
-                        e = INFINITY;                               // A, left out, might count
-                    }
-                }
+                const float d = mul_rn(d0, pw[q]);
+                const bool out = valid && !want_delta && !(fabsf((mq[q] - A.x) + d) <= A.y);
+                const TermBound tb = bounded_term<EM>(A, Bv, share, mq[q], d, out);
                 // (and the rounding of the sums of centres)
                 if (valid) {
-                    const bool known = e + trunc < INFINITY;
-                    cen += known ? c : 0.0f;
-                    err += known ? fmaf(1.3e-6f, fabsf(c), e + trunc) : INFINITY;
+                    cen += tb.c;
+                    err += fmaf(1.3e-6f, fabsf(tb.c), tb.e);
                 }
                 const uint64_t bal = __ballot(out);
                 if (bal) {

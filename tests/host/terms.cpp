@@ -1,7 +1,7 @@
-// The likelihood terms of bdc_device.h on the host, for test_term_bounds.py.
+// The likelihood terms of bdc_device.h and bdc_bounds.h on the host, for test_term_bounds.py.
 #include "builtins.h"
 
-#include "bdc_device.h"
+#include "bdc_bounds.h"
 
 using namespace bdc;
 
@@ -60,6 +60,28 @@ void bounds(int n, const float* c, const float* a2, const float* m0, const float
         half[i] = t.e;
         value[i] = delta_ell_direct(mu, d, pc, terms);
         radius[i] = s.b.y <= 0.0f ? (fabsf(y) <= s.R ? 0.0 : (double)s.R) : -1.0;
+    }
+}
+
+// EMCCD: interval of the bounded pass and direct evaluation of moves mu -> mu + d, mu = m +
+// shift times the reach of the series at m, with the record's log A and -c - log G.
+void emccd(int n, const float* c, const float* lA, const float* lB, const float* m, const float* shift, const float* step,
+           double* centre, double* half, double* value) {
+    for (int i = 0; i < n; ++i) {
+        const EmSeries es = emccd_series(m[i], c[i], lA[i], lB[i]);
+        const float reach = m[i] * (fabsf(es.s.b.x) + 1.0f) < 1e5f ? fminf(BND_R * es.s.R, 0.5f * m[i]) : 0.0f;
+        const float mu = m[i] + shift[i] * reach, d = mu * step[i];
+        PixConst pc;
+        pc.c = c[i];
+        pc.a2 = -1.0f;
+        pc.L0 = lA[i];
+        pc.iB = lB[i];
+        const bool out = !(fabsf((mu - m[i]) + d) <= reach);
+        const TermBound t = bounded_term<true>(make_float4(m[i], reach, es.s.b.x, es.s.b.y), make_float2(es.s.b.z, es.s.b.w),
+                                               es.w, mu, d, out);
+        centre[i] = t.c;
+        half[i] = t.e;
+        value[i] = delta_ell_emccd(mu, d, pc);
     }
 }
 

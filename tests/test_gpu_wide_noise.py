@@ -29,3 +29,16 @@ def test_sweeps_reach_the_state_of_direct_decisions(bdc, case):  # noqa: F811
     ra, la, _ = A.rho()
     rb, lb, _ = B.rho()
     assert np.array_equal(ra, rb) and np.array_equal(la, lb)
+
+
+# EMCCD: zero-photon normal of 8 to 60 photons' width, so that it and the amplified photons take turns in dominating
+@pytest.mark.parametrize("s,level,noise", [(11, 5.0, 16.0), (15, 40.0, 60.0), (21, 20.0, 120.0)])
+def test_emccd_sweeps_reach_the_state_of_direct_decisions(bdc, s, level, noise):  # noqa: F811
+    psf = synth.gaussian_psf((s - 1) / 8.0, s)
+    img, cam = lattice_frame(45, 50, 1, psf, 60 + s, 1, level, noise)
+    A, B = twins(bdc, img, cam, psf, bdc.BDC_SCHED_BLOCK, 0, 2, 5 + s, 4, camera=1)
+    A.sweep(6)
+    advance_by_groups(B, 6)
+    ra, la, _ = A.rho()
+    rb, lb, _ = B.rho()
+    assert np.array_equal(ra, rb) and np.array_equal(la, lb)

@@ -116,3 +116,33 @@ def test_intervals_hold_the_direct_evaluation(terms, noise):
     excess = np.abs(value - centre) - (1.02 * half + 1e-7)
     assert np.isfinite(value[tell]).all()
     assert excess[tell].max() <= 0.0, (excess[tell].max(), np.flatnonzero(tell)[excess[tell].argmax()])
+
+
+@pytest.mark.parametrize("noise", [(0.3, 3.0), (3.0, 20.0), (20.0, 100.0)], ids=lambda v: "%gto%g" % v)
+def test_emccd_intervals_hold_the_direct_evaluation(terms, noise):
+    """The reading is a mixture of the zero-photon normal (A) and the amplified photons (B f): an
+    interval of the bounded pass holds its direct evaluation whichever of the two dominates at the
+    anchor, at the present mean (anywhere in the series' reach) and at the proposed one.  The pass
+    adds 1.3e-6 of the centre and 1e-7 a term, and decides at 1.02 half-widths and 1e-7."""
+    rng = np.random.default_rng(int(noise[0] * 100))
+    n = 150000
+    sg = np.exp(rng.uniform(np.log(noise[0]), np.log(noise[1]), n))          # read noise over gain, photons
+    gain = 20.0
+    true = np.exp(rng.uniform(np.log(0.02), np.log(3000.0), n))
+    phi = rng.poisson(true)
+    c = np.where(phi > 0, rng.gamma(np.maximum(phi, 1), 1.0), sg * rng.standard_normal(n))
+    m = true * np.exp(rng.normal(0.0, 0.8, n))
+    shift = np.where(rng.random(n) < 0.2, 0.0, rng.uniform(-1.0, 1.0, n))
+    step = np.expm1(np.clip(rng.normal(0.0, 1.0, n) * np.where(rng.random(n) < 0.6, 0.3, 2.0), -3.8, 6.0))
+    # a mean drifted by the whole reach to where A dominates; A only just out of FP32's sight
+    sg[:2], c[:2], m[:2], shift[:2], step[:2] = [87.9, 36.0], [1910.92, 89.7], [375.136, 29.5], [-0.997, 0.0], [0.0918, -0.2045]
+    c = np.float32(c)
+    s = sg * gain
+    lA = -0.5 * np.log(2.0 * np.pi * s ** 2) - (c.astype(np.float64) * gain) ** 2 / (2.0 * s ** 2)
+    lB = np.where(c > 0, -c.astype(np.float64) - np.log(gain), -np.inf)
+    centre, half, value = call(terms.emccd, n, [c, lA, lB, m, shift, step], [np.float64] * 3)
+    tell = np.isfinite(half)
+    assert tell.mean() > 0.7
+    excess = np.abs(value - centre) - (1.02 * (half + 1.3e-6 * np.abs(centre) + 1e-7) + 1e-7)
+    assert np.isfinite(value[tell]).all()
+    assert excess[tell].max() <= 0.0, (excess[tell].max(), np.flatnonzero(tell)[excess[tell].argmax()])
