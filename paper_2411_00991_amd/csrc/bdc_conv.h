@@ -138,12 +138,23 @@ struct ConvTile {
 //   2^24     982     713     627     587     410
 // (the lines lie at the same n for PSFs of 11 x 11 and 63 x 63): few outputs
 // need more waves and shorter chains, many need fewer reads and conversions.
+//
+// The mean refresh keeps to four parts of the PSF columns at any size: a split is an
+// order of the FP64 sum, and a chain's means must not depend on how many chains share
+// the launch or on whether its tile runs in a batch (whose items take <8, 4>).  That
+// costs a refresh of 2^24 means 7 % (a sweep of 2048 x 2048, four chains, 0.1 %).
 template <class F>
-hipError_t conv_dispatch(int64_t n, F&& launch) {
-    if (n >= 1 << 20) return launch(ConvTile<8, 2>{});
+hipError_t conv_dispatch_chains(int64_t n, F&& launch) {
     if (n >= 1 << 18) return launch(ConvTile<8, 4>{});
     if (n >= 1 << 16) return launch(ConvTile<4, 4>{});
     return launch(ConvTile<2, 4>{});
+}
+
+// Richardson-Lucy, one image per launch: also two parts.
+template <class F>
+hipError_t conv_dispatch(int64_t n, F&& launch) {
+    if (n >= 1 << 20) return launch(ConvTile<8, 2>{});
+    return conv_dispatch_chains(n, launch);
 }
 
 }  // namespace bdc

@@ -2621,7 +2621,7 @@ hipError_t launch_forward_propose(const Frame& f, const State& S, const Prior& p
         if (propose) hipLaunchKernelGGL(k_propose_sub, dim3(grid1(f.N), f.C), dim3(WG), 0, st, f, S, pr);
         return hipGetLastError();
     }
-    return conv_dispatch(f.N * f.C, [&](auto t) {
+    return conv_dispatch_chains(f.N * f.C, [&](auto t) {
         using T = decltype(t);
         hipLaunchKernelGGL(k_forward_propose<T>, dim3(T::tiles(f.H, f.W), f.C), dim3(WG), T::lds(f.r), st, f, S, pr,
                            propose);
