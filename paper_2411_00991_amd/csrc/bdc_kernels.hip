@@ -296,7 +296,7 @@ __device__ inline bool decide_commit(const Frame& f, const State& S, int chain, 
         }
         if (t < burn_in) {
             const float gain = exp2f(-0.6f * log2f((float)t + 1.0f));
-            S.log_step[i] += gain * ((acc ? 1.0f : 0.0f) - 0.44f);
+            S.log_step[i] = fmaf(gain, (acc ? 1.0f : 0.0f) - 0.44f, S.log_step[i]);
         }
         if (dbg_delta) dbg_delta[i] = (float)delta;
         if (dbg_acc) dbg_acc[i] = acc ? 1 : 0;
@@ -348,7 +348,7 @@ __global__ void __launch_bounds__(WG) k_colour_pass(Frame f, State S, int burn_i
         const int ny = y + j / s - r, nx = x + j % s - r;
         if (ny < 0 || ny >= f.H || nx < 0 || nx >= f.W) continue;
         const int64_t n = (int64_t)ny * f.W + nx;
-        part += delta_pix<EM>(mu[n], d * f.psf[j], load_pc(f.pc, n), inv_tab, nterms);
+        part += delta_pix<EM>(mu[n], mul_rn(d, f.psf[j]), load_pc(f.pc, n), inv_tab, nterms);
         ++nevals;
     }
     count_work(S.counters, nterms, nevals);
@@ -367,7 +367,8 @@ __global__ void __launch_bounds__(WG) k_colour_pass(Frame f, State S, int burn_i
         for (int j = threadIdx.x; j < F; j += WG) {
             const int ny = y + j / s - r, nx = x + j % s - r;
             if (ny < 0 || ny >= f.H || nx < 0 || nx >= f.W) continue;
-            muw[(int64_t)ny * f.W + nx] += d * f.psf[j];
+            float& m = muw[(int64_t)ny * f.W + nx];
+            m = fmaf(d, f.psf[j], m);
         }
     }
 }
@@ -396,7 +397,7 @@ __global__ void __launch_bounds__(WG) k_colour_pass_sub(Frame f, State S, int bu
         const int ny = py + j / s - r, nx = px + j % s - r;
         if (ny < 0 || ny >= f.Hp || nx < 0 || nx >= f.Wp) continue;
         const int64_t n = (int64_t)ny * f.Wp + nx;
-        part += delta_pix<EM>(mu[n], d * T[j], load_pc(f.pc, n), inv_tab, nterms);
+        part += delta_pix<EM>(mu[n], mul_rn(d, T[j]), load_pc(f.pc, n), inv_tab, nterms);
         ++nevals;
     }
     count_work(S.counters, nterms, nevals);
@@ -415,7 +416,8 @@ __global__ void __launch_bounds__(WG) k_colour_pass_sub(Frame f, State S, int bu
         for (int j = threadIdx.x; j < F; j += WG) {
             const int ny = py + j / s - r, nx = px + j % s - r;
             if (ny < 0 || ny >= f.Hp || nx < 0 || nx >= f.Wp) continue;
-            muw[(int64_t)ny * f.Wp + nx] += d * T[j];
+            float& m = muw[(int64_t)ny * f.Wp + nx];
+            m = fmaf(d, T[j], m);
         }
     }
 }
@@ -601,7 +603,7 @@ __device__ void block_phase_block(const Frame& f, const State& S, int burn_in, c
                 const int o = s_off[j], oy = o & 0xFF, ox = o >> 8;
                 const float muv = s_mu[rbase + oy * RW + ox];
                 const int64_t n = m + (int64_t)(oy - r) * f.W + (ox - r);
-                part += delta_pix<EM>(muv, d * s_psf[j], load_pc(f.pc, n), s_inv, nterms);
+                part += delta_pix<EM>(muv, mul_rn(d, s_psf[j]), load_pc(f.pc, n), s_inv, nterms);
                 ++nevals;
             }
             part = wave_sum(part);
@@ -619,7 +621,7 @@ __device__ void block_phase_block(const Frame& f, const State& S, int burn_in, c
                     const float muv = s_mu[rbase + oy * RW + ox];
                     if (muv < 0.0f) continue;                     // outside the frame
                     const int64_t n = m + (int64_t)(oy - r) * f.W + (ox - r);
-                    part += delta_pix<EM>(muv, d * s_psf[j], load_pc(f.pc, n), s_inv, nterms);
+                    part += delta_pix<EM>(muv, mul_rn(d, s_psf[j]), load_pc(f.pc, n), s_inv, nterms);
                     ++nevals;
                 }
                 part = wave_sum(part);
@@ -644,7 +646,7 @@ __device__ void block_phase_block(const Frame& f, const State& S, int burn_in, c
                     const int ri = rbase + (o & 0xFF) * RW + (o >> 8);
                     const float muv = s_mu[ri];
                     if (muv < 0.0f) continue;
-                    s_mu[ri] = muv + d * s_psf[j];
+                    s_mu[ri] = fmaf(d, s_psf[j], muv);
                 }
             }
         }
@@ -730,7 +732,7 @@ __global__ void __launch_bounds__(WG) k_block_phase_sub(Frame f, State S, int bu
                 const float muv = s_mu[rbase + oy * RW + ox];
                 if (muv < 0.0f) continue;                     // outside the frame
                 const int64_t n = (int64_t)(by0 + ly + oy - r) * f.Wp + (bx0 + lx + ox - r);
-                part += delta_pix<EM>(muv, d * T[j], load_pc(f.pc, n), s_inv, nterms);
+                part += delta_pix<EM>(muv, mul_rn(d, T[j]), load_pc(f.pc, n), s_inv, nterms);
                 ++nevals;
             }
             part = wave_sum(part);
@@ -750,7 +752,7 @@ __global__ void __launch_bounds__(WG) k_block_phase_sub(Frame f, State S, int bu
                     const int ri = rbase + (o & 0xFF) * RW + (o >> 8);
                     const float muv = s_mu[ri];
                     if (muv < 0.0f) continue;
-                    s_mu[ri] = muv + d * T[j];
+                    s_mu[ri] = fmaf(d, T[j], muv);
                 }
             }
         }
@@ -1290,7 +1292,7 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
                 row_rho = rp;
                 row_acc = true;
             }
-            row_ls += gain * ((acc ? 1.0f : 0.0f) - 0.44f);
+            row_ls = fmaf(gain, (acc ? 1.0f : 0.0f) - 0.44f, row_ls);
         }
         n_acc += acc ? 1 : 0;
         if (threadIdx.x == 0) {
@@ -1633,7 +1635,7 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
         if (lane == lx) {
             row_rho = acc ? rp : row_rho;
             row_acc = row_acc || acc;
-            row_ls += gain * ((acc ? 1.0f : 0.0f) - 0.44f);
+            row_ls = fmaf(gain, (acc ? 1.0f : 0.0f) - 0.44f, row_ls);
         }
         n_acc += acc ? 1 : 0;
         if (lane == 0) {
