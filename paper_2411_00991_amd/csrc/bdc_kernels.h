@@ -7,8 +7,19 @@
 #include <stdint.h>
 
 #include "bdc_consts.h"
+#include "bdc_once.h"
 
 namespace bdc {
+
+// Dynamic LDS up to bytes for a kernel, on the current device.
+inline hipError_t allow_lds(OncePerDevice& once, const void* kernel, size_t bytes) {
+    int device = -1;
+    const hipError_t e = hipGetDevice(&device);
+    if (e != hipSuccess) return e;
+    return once.run(device, hipSuccess, [&] {
+        return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    });
+}
 
 struct Frame {                     // one frame (or one tile of a batch)
     int H, W, s, r;                // object lattice size, footprint side and radius

@@ -2692,9 +2692,9 @@ static hipError_t launch_bounded_as(const Frame& f, const State& S, int burn_in,
     const int nblk = ((nby - py + 1) / 2) * ((nbx - px + 1) / 2);
     if (nblk <= 0) return hipSuccess;
     auto kern = k_block_bounded<EM, DIR, SUB, NT, NQ>;
-    static const hipError_t attr =
-        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)BND_LDS_MAX);
-    if (attr != hipSuccess) return attr;
+    static OncePerDevice once;
+    const hipError_t e = allow_lds(once, (const void*)kern, BND_LDS_MAX);
+    if (e != hipSuccess) return e;
     const size_t lds = bounded_layout(B, f.s, EM, DIR, nullptr, nullptr);
     hipLaunchKernelGGL(kern, xcd_grid(nblk, f.C), dim3(NT), lds, st, f, S, burn_in, inv_tab, B, py, px, k0, k1,
                        dbg_delta, dbg_acc, nblk);
@@ -2828,13 +2828,9 @@ hipError_t launch_block_series(const Frame& f, const State& S, int burn_in, cons
     const int nby_p = (nby - py + 1) / 2, nbx_p = (nbx - px + 1) / 2;
     if (nby_p <= 0 || nbx_p <= 0) return hipSuccess;
     const size_t lds = block_series_lds(B, f.s);
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_block_series, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)BLOCK_SERIES_LDS_MAX);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
+    static OncePerDevice once;
+    const hipError_t e = allow_lds(once, (const void*)k_block_series, BLOCK_SERIES_LDS_MAX);
+    if (e != hipSuccess) return e;
     (void)inv_tab;   // the pass computes its reciprocals (no table in its LDS budget)
     const int nblk = nby_p * nbx_p;
     hipLaunchKernelGGL(k_block_series, xcd_grid(nblk, f.C), dim3(WG), lds, st, f, S, burn_in, B, py, px, k0, k1,

@@ -95,13 +95,9 @@ size_t quantile_lds(int64_t n) {
 hipError_t launch_quantiles(const float* v, int64_t n, int64_t stride, int64_t n_pix, const float* probs, int n_probs,
                             float* out, hipStream_t st) {
     if (n < 1 || n > QMAX || n_pix < 1) return hipErrorInvalidValue;
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_quantiles, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)quantile_lds(QMAX));
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
+    static OncePerDevice once;
+    const hipError_t e = allow_lds(once, (const void*)k_quantiles, quantile_lds(QMAX));
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_quantiles, dim3(grid_n(n_pix, WG / QW)), dim3(WG), quantile_lds(n), st, v, n, stride, n_pix,
                        probs, n_probs, out);
     return hipGetLastError();
