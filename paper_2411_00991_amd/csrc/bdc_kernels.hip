@@ -869,7 +869,7 @@ __global__ void __launch_bounds__(WG) k_chunk_fourier(Frame f, State S, MomentBu
 // always do, so the chain is the same bit for bit.  What an update waited for
 // was one dependent chain of direct evaluations on a few lanes; 2048 x 2048, 4
 // chains, Airy 31 x 31: 147.6 to 121.1 ms for two sweeps (17.9 to 14.7 ms per
-// launch), direct evaluations 32 to 0.16 per update; 512 x 512, one chain (one
+// launch), direct evaluations 32 to 0.02 per update; 512 x 512, one chain (one
 // workgroup per CU, all latency): 46.1 to 35.5 ms for four sweeps.
 // An accepted move re-anchors the pixels that left their radius (|D + d| > R:
 // the old series is spent).  Those of the PSF core are queued in LDS with their
@@ -880,7 +880,7 @@ __global__ void __launch_bounds__(WG) k_chunk_fourier(Frame f, State S, MomentBu
 // [2] direct evaluations, [3] series anchored (new ring rows, accepted moves
 // out of the radius), [4] their phi terms.
 // ---------------------------------------------------------------------------
-constexpr int SER_Q = 4;                      // footprint entries per thread (F <= SER_Q * WG)
+constexpr int SER_Q = 4;                      // footprint entries per thread, at most (F <= SER_Q * WG)
 constexpr int SER_JOBS = 48;                  // queued pixels to re-anchor; beyond, the owner lanes
 
 __device__ inline void count_work5(unsigned long long* ctr, int terms, int evals, int direct, int anchors,
@@ -1067,6 +1067,7 @@ __host__ __device__ inline int block_series_jobs(int B, int s) {
     return n < SER_JOBS ? (int)n : SER_JOBS;
 }
 
+template <int NQ>
 __device__ void block_series_block(const Frame& f, const State& S, int burn_in, int B,
                                    int py, int px, int bi, int chain, int64_t t, int k0, int k1, float* dbg_delta,
                                    uint8_t* dbg_acc, double* lds_d) {
@@ -1095,17 +1096,17 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
 
     // this thread's footprint entries, the heaviest PSF weights first:
     // offsets (oy, ox) packed as oy | ox << 8, and the weight
-    int off[SER_Q];
-    float pw[SER_Q];
+    int off[NQ];
+    float pw[NQ];
 #pragma unroll
-    for (int q = 0; q < SER_Q; ++q) {
+    for (int q = 0; q < NQ; ++q) {
         const int e = threadIdx.x + q * WG;
         const int j = e < F ? (int)f.psf_order[e] : -1;
         off[q] = j >= 0 ? ((j / s) | ((j % s) << 8)) : -1;
         pw[q] = j >= 0 ? f.psf[j] : 0.0f;
     }
     const int oy0 = off[0] & 0xFF, ox0 = (off[0] >> 8) & 0xFF;
-    // padding entries (F < SER_Q * WG) read the sink cell: outside the frame
+    // padding entries (F < NQ * WG) read the sink cell: outside the frame
     if (threadIdx.x == 0) {
         ring.A[NR] = make_float4(0.0f, -1.0f, 0.0f, 0.0f);
         ring.B[NR] = make_float2(0.0f, 0.0f);
@@ -1123,11 +1124,11 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
     }
     int ly_cur = ly;
     // ring index of each entry at column 0 of the current block row
-    int rb[SER_Q];
+    int rb[NQ];
     auto row_bases = [&](int y) {
         const int slot0 = y % s;
 #pragma unroll
-        for (int q = 0; q < SER_Q; ++q) {
+        for (int q = 0; q < NQ; ++q) {
             const int oy = off[q] & 0xFF, ox = (off[q] >> 8) & 0xFF;
             int slot = slot0 + oy;
             slot = slot >= s ? slot - s : slot;
@@ -1196,11 +1197,11 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
         }
         const int64_t m = (int64_t)(by0 + ly) * f.W + (bx0 + lx);
         // 1. every entry's records, loads issued together
-        int ri[SER_Q];
-        float4 Aq[SER_Q];
-        float2 Bq[SER_Q];
+        int ri[NQ];
+        float4 Aq[NQ];
+        float2 Bq[NQ];
 #pragma unroll
-        for (int q = 0; q < SER_Q; ++q) {
+        for (int q = 0; q < NQ; ++q) {
             ri[q] = off[q] >= 0 ? rb[q] + lx : NR;
             Aq[q] = ring.A[ri[q]];
             Bq[q] = ring.B[ri[q]];
@@ -1211,9 +1212,9 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
         // terms' magnitudes.)  A pixel that an accepted move takes out of its
         // radius is queued: for the PSF core with the record fetched an update
         // ahead, else with its pixel (marked by a negative 2a).
-        bool fast[SER_Q], any = false;
+        bool fast[NQ], any = false;
         unsigned left = 0;                                          // entries beyond the queue; bit 8: the first is one
-        float y[SER_Q], fpart = 0.0f, gpart = 0.0f, err = 0.0f;
+        float y[NQ], fpart = 0.0f, gpart = 0.0f, err = 0.0f;
         // slot i of the queue's round: (mu, d) for a lane's first such pixel,
         // re-anchored over the window of its move, (mu + d, 0) for further ones,
         // over that of the new mean
@@ -1224,7 +1225,7 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
             job_ri[i] = ri[q];
         };
 #pragma unroll
-        for (int q = 0; q < SER_Q; ++q) {
+        for (int q = 0; q < NQ; ++q) {
             const float dq = mul_rn(d0, pw[q]);
             y[q] = entry_y(q == 0, Aq[q].x, d0, pw[q]);
             const bool valid = Aq[q].y >= 0.0f;
@@ -1301,7 +1302,7 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
         }
         if (acc) {
 #pragma unroll
-            for (int q = 0; q < SER_Q; ++q)
+            for (int q = 0; q < NQ; ++q)
                 if (fast[q]) ring.A[ri[q]].x = y[q];
             // pixels that left their series' radius: re-anchor at the new mean
             auto anchor = [&](int i, const Series& nx, float mu1) {
@@ -1324,7 +1325,7 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
                 if (threadIdx.x == 0) s_cnt[3] = 0;
                 lds_barrier();
 #pragma unroll
-                for (int q = 0; q < SER_Q; ++q) {
+                for (int q = 0; q < NQ; ++q) {
                     const uint64_t bal = __ballot((left >> q) & 1);
                     if (!bal) continue;
                     int i = 0;
@@ -1349,13 +1350,14 @@ __device__ void block_series_block(const Frame& f, const State& S, int burn_in, 
     count_work5(S.counters, nterms, nevals, ndirect, nanch, aterms);
 }
 
+template <int NQ>
 __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3))) k_block_series(Frame f, State S, int burn_in, int B,
                                                      int py, int px, int k0, int k1, float* dbg_delta,
                                                      uint8_t* dbg_acc, int nblk) {
     extern __shared__ double lds_d[];
     int bi, chain;
     if (!xcd_block(nblk, f.C, bi, chain)) return;
-    block_series_block(f, S, burn_in, B, py, px, bi, chain, *S.t, k0, k1, dbg_delta, dbg_acc, lds_d);
+    block_series_block<NQ>(f, S, burn_in, B, py, px, bi, chain, *S.t, k0, k1, dbg_delta, dbg_acc, lds_d);
 }
 
 // ---------------------------------------------------------------------------
@@ -2828,14 +2830,22 @@ hipError_t launch_block_series(const Frame& f, const State& S, int burn_in, cons
     const int nby_p = (nby - py + 1) / 2, nbx_p = (nbx - px + 1) / 2;
     if (nby_p <= 0 || nbx_p <= 0) return hipSuccess;
     const size_t lds = block_series_lds(B, f.s);
-    static OncePerDevice once;
-    const hipError_t e = allow_lds(once, (const void*)k_block_series, BLOCK_SERIES_LDS_MAX);
-    if (e != hipSuccess) return e;
     (void)inv_tab;   // the pass computes its reciprocals (no table in its LDS budget)
     const int nblk = nby_p * nbx_p;
-    hipLaunchKernelGGL(k_block_series, xcd_grid(nblk, f.C), dim3(WG), lds, st, f, S, burn_in, B, py, px, k0, k1,
-                       dbg_delta, dbg_acc, nblk);
-    return hipGetLastError();
+    auto go = [&](auto entries) {
+        auto kern = k_block_series<decltype(entries)::value>;
+        static OncePerDevice once;
+        const hipError_t e = allow_lds(once, (const void*)kern, BLOCK_SERIES_LDS_MAX);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, xcd_grid(nblk, f.C), dim3(WG), lds, st, f, S, burn_in, B, py, px, k0, k1, dbg_delta,
+                           dbg_acc, nblk);
+        return hipGetLastError();
+    };
+    // Three entries per thread hold the footprints up to side 27, four all up to 31.  The
+    // fourth of the smaller ones is padding that every update reads: six sweeps of 301 x 388, 4
+    // chains, scalar camera, four and three entries: side 23 25.4 and 24.3 ms, side 25
+    // 30.3 and 28.8, side 27 35.9 and 34.1.  (A batch runs all its tiles with four.)
+    return f.s * f.s <= 3 * WG ? go(std::integral_constant<int, 3>{}) : go(std::integral_constant<int, SER_Q>{});
 }
 
 hipError_t launch_moments(const Frame& f, const State& S, const Prior& pr, const MomentBufs& M, int burn_in,
@@ -2975,7 +2985,7 @@ k_batch(const TileDesc* tiles, const Item* items, const double* inv_tab) {
     if constexpr (KIND == BK_FORWARD) {
         forward_tile<BatchConv>(T.f, T.S, T.pr, 1, I.index, I.chain, t, (float*)lds_b);
     } else if constexpr (KIND == BK_SERIES) {
-        block_series_block(T.f, T.S, T.burn_in, T.B, ph / 2, ph % 2, I.index, I.chain, t, 0, T.f.s * T.f.s,
+        block_series_block<SER_Q>(T.f, T.S, T.burn_in, T.B, ph / 2, ph % 2, I.index, I.chain, t, 0, T.f.s * T.f.s,
                            nullptr, nullptr, lds_b);
     } else if constexpr (KIND == BK_PHASE || KIND == BK_PHASE_EM) {
         block_phase_block<KIND == BK_PHASE_EM>(T.f, T.S, T.burn_in, inv_tab, T.B, ph / 2, ph % 2, I.index,
