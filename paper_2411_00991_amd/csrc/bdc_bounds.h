@@ -89,7 +89,7 @@ __device__ inline TermBound bounded_term(float4 A, float2 Bv, float share, float
     const float ym = out ? fabsf(D) : fmaxf(fabsf(y), fabsf(D)), y2 = ym * ym;
     const float trunc = fabsf(b.w) * (y2 * y2) * (3.2f * ym * fast_rcp(A.x));
     t.c = d * series_slope(b, D, y);
-    t.e = BND_REL * cnt * fabsf(d);
+    t.e = rounding_of(A.x, b, cnt) * fabsf(d);
     if (out) t = series_bound(A.x, b, D, y, t.c);
     if (EM) {
         const float gD = fmaf(D, series_slope(b, 0.0f, D), D), gy = gD + t.c + d;

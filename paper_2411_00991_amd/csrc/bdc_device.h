@@ -764,18 +764,24 @@ __device__ inline Series series_after(float mu, float d, const PixConst& pc, int
 // [0, 1] and Jensen's inequality give for every v > 0, used from v = 1 on,
 //   (E^2 / s2) log(1 + s2 v / E) <= sum <= (E - s2) v + s2 log(1 + v).
 // At D the series is within TAU / 2.  The direct evaluation and the coefficients round
-// too: FP32 logs (a few 1e-7 of E |v|, over 1 - |v| for v < 0) and, at read noise of
-// several photons, exp(2a) in FP32 over windows of up to 128 terms; BND_REL covers
-// both.  log(1 + v) here is off by at most 2e-7 of E; 1e-6 is added.  Over 24 M terms
-// of read noise from 0.05 to 100 photons and means from 0.05 to 3000, instructions
-// rounded either way, no direct evaluation lay outside (with 4e-6, one in 200 at 10
-// photons; with 4e-5, one); the wider interval costs no time (512 x 512: 35.4 ms).  Not
-// covered: a series formed over the window of a move that took the mean to less than
-// 1/100, as its 1 + d / mu is off by more.  Infinite where nothing is claimed: no series
-// (b2 > 0), y at the edge of -m, and counts so large that the direct window may be
-// refused.
+// too: FP32 logs, a few 1e-7 of E |v|, over 1 - |v| for v < 0 (BND_LOG); and exp(2a) in
+// FP32, whose error over a window of n terms is n 1e-7 of the change of the mean count.
+// That change is at most (E - s2) |v|, over 1 - |v| for v < 0, as E - s2 is the count's
+// variance: next to nothing where read noise is sharp, all of E where it is wide and
+// windows are long (BND_EXP, n up to 128 twice and what an earlier window left in the
+// coefficients).  log(1 + v) here is off by at most 2e-7 of E; 1e-6 is added.  Over 24 M
+// terms of read noise from 0.05 to 100 photons and means from 0.05 to 3000, instructions
+// rounded either way, no direct evaluation lay outside (4e-6 of E |v| alone: one in 200 at
+// 10 photons).  Not covered: a series formed over the window of a move that took the mean
+// to less than 1/100, as its 1 + d / mu is off by more.  Infinite where nothing is
+// claimed: no series (b2 > 0), y at the edge of -m, and counts so large that the direct
+// window may be refused.
 struct TermBound { float c, e; };
-constexpr float BND_REL = 6e-5f;
+constexpr float BND_LOG = 4e-6f, BND_EXP = 6e-5f;
+// Of |d|, before the 1 - |v|: m the anchor, b its coefficients, cnt = E / m.
+__device__ inline float rounding_of(float m, float4 b, float cnt) {
+    return fmaf(BND_EXP, fmaf(2.0f * b.y, m, cnt), BND_LOG * cnt);
+}
 
 // sd: series_delta(b, D, y - D).
 __device__ inline TermBound series_bound(float m, float4 b, float D, float y, float sd) {
@@ -798,7 +804,7 @@ __device__ inline TermBound series_bound(float m, float4 b, float D, float y, fl
         t.c = 0.5f * (hi + lw) - y - series_delta(b, 0.0f, D);
         t.e = 0.5f * fabsf(hi - lw);
     }
-    t.e = fmaf(cnt * scale, fmaf(BND_REL, ay + fabsf(D), 1e-6f * m), t.e + 1.6e-9f);
+    t.e = fmaf(scale, fmaf(rounding_of(m, b, cnt), ay + fabsf(D), 1e-6f * cnt * m), t.e + 1.6e-9f);
     if (!(b.y <= 0.0f && (v > 0.0f || den > 0.02f * m) && cnt * (m + ay) < 2.5e5f && t.e < INFINITY)) {
         t.c = 0.0f;
         t.e = INFINITY;
