@@ -1052,7 +1052,7 @@ __device__ inline DirectPart block_direct_part(const Frame& f, const Ring& ring,
 
 // Slots of the re-anchoring queue: up to SER_JOBS, fewer where the ring leaves
 // less room below the LDS size at which one more workgroup fits on a CU (the
-// ring of a 31 x 31 PSF at B = 31 leaves 25).
+// ring of a 31 x 31 PSF at B = 31 leaves 24).
 constexpr int SER_JOB_BYTES = sizeof(float4) + sizeof(float2) + sizeof(int);
 __host__ __device__ inline size_t block_series_fixed(int B, int s) {
     const int RW = B + 2 * (s / 2);
@@ -2675,7 +2675,10 @@ static dim3 xcd_grid(int nblk, int C) {
 }
 
 // The bounded pass takes the readings, priors and lattices that have no series
-// scan, with one cell per block and colour and a region within the LDS.  It was
+// scan, with one cell per block and colour and a region within the LDS.  Outside it are
+// the blocks of B = 8 that AUTO gives to footprints below side 8 (several cells per
+// colour), EMCCD sides from 37 on and the EMCCD tiles of a batch, whose items share one
+// workgroup of four waves and 64 KB: these run the all-direct pass, several times slower.  It was
 // the faster one at every size tried, from 100 x 134 (PSF 11, 3 chains: 1.8 against
 // 9.1 ms for two sweeps of the all-direct pass) to 1536^2 (PSF 31, 4 chains: 130 against
 // 1358 ms).  Larger blocks and regions keep the all-direct pass.

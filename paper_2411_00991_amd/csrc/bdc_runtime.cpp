@@ -279,8 +279,8 @@ void choose_schedule(bdc_ctx* c) {
         return;
     }
     if (c->cfg.camera == BDC_CAMERA_EMCCD) {
-        // the truncation-bounded local series is derived for the sCMOS reading;
-        // an EMCCD pixel's likelihood change is the closed form in every pass
+        // the series scans evaluate the sCMOS reading; an EMCCD pixel's likelihood change is
+        // the closed form (which the bounded block pass decides most moves without)
         if (sched == BDC_SCHED_BLOCK_SERIES || sched == BDC_SCHED_BLOCK9_SERIES)
             fail(BDC_EINVAL, "the block-series scans take the sCMOS reading only");
         if (sched == BDC_SCHED_AUTO)

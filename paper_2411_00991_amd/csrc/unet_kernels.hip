@@ -564,10 +564,10 @@ constexpr int HALO_PP = 40;        // LDS elements per halo pixel (32 channels +
 inline bool frag_order(int ci, int co) { return ci % 32 == 0 && co % 32 == 0; }
 
 // waves per SIMD that the shape's registers leave
-constexpr int halo_waves(int tm, int tn) { return tm == 8 ? 1 : tn == 1 ? 4 : tn == 2 ? 3 : 2; }
+constexpr int halo_waves(int tn) { return tn == 1 ? 4 : tn == 2 ? 3 : 2; }
 
 template <int TM, int TN, int WX, int WY, int WN, class EP>
-__global__ void __launch_bounds__(64 * WX * WY * WN) __attribute__((amdgpu_waves_per_eu(halo_waves(TM, TN))))
+__global__ void __launch_bounds__(64 * WX * WY * WN) __attribute__((amdgpu_waves_per_eu(halo_waves(TN))))
 k_conv3_halo(Tens x, const uint16_t* wf, int K, EP ep, int N,
                                                                   int tiles) {
     constexpr int NTH = 64 * WX * WY * WN, TW = 16 * WX, TH = TM * WY, HW = TW + 2, HH = TH + 2, BN = 16 * TN * WN;
@@ -706,14 +706,17 @@ hipError_t conv_halo_as(const Tens& x, const uint16_t* wf, int K, const EP& ep, 
     const int64_t tiles = (int64_t)tx * ty * (P / ((int64_t)x.H * x.W));
     if (tiles > (1 << 30)) return hipErrorInvalidValue;
     // workgroups: a multiple of the dies, no more than are resident
-    const int64_t groups = std::min<int64_t>((tiles + XCDS - 1) / XCDS, std::max(1, 32 * halo_waves(TM, TN) / ny)) * XCDS;
+    const int64_t groups = std::min<int64_t>((tiles + XCDS - 1) / XCDS, std::max(1, 32 * halo_waves(TN) / ny)) * XCDS;
     hipLaunchKernelGGL((k_conv3_halo<TM, TN, WX, WY, WN, EP>), dim3((unsigned)groups, ny), dim3(64 * WX * WY * WN), 0, st, x,
                        wf, K, ep, N, (int)tiles);
     return hipGetLastError();
 }
 
-// Whether the halo kernel covers this input: 32-channel slabs, an output
-// channel count that is a multiple of 32, tile rows that divide the image.
+// Whether a layer runs the halo kernel: 32-channel slabs, an output channel count that
+// is a multiple of 32, and sizes that make whole tiles of 128 pixels.  The kernel masks
+// the frame's edge and needs no rule on the sizes; layers of other sizes (the deep
+// levels of ragged frames) run k_gemm, which sums in another order, and the two
+// have not been timed against each other there.
 inline bool halo_ok(const Tens& x, int N) {
     if (x.C % 32 != 0 || N % 32 != 0 || x.ld % 8 != 0 || x.off % 8 != 0) return false;
     const int TW = x.W % 32 == 0 ? 32 : (x.W % 16 == 0 ? 16 : (x.W % 8 == 0 ? 8 : 0));
