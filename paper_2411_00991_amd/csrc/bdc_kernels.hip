@@ -1612,7 +1612,9 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
 #pragma unroll 1
                 for (int j = lane; j < min(nq, QCAP); j += 64) {
                     const float4 jb = jobs[j];
-                    part += delta_ell_direct(jb.x, jb.y, pc_from(jb.z, jb.w), nterms);
+                    const DirectValue dv = direct_value(jb.x, jb.y, pc_from(jb.z, jb.w));
+                    part += dv.v;
+                    nterms += dv.terms;
                     ++ndirect;
                 }
                 if (nq > QCAP) {
@@ -1623,7 +1625,9 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
                             float dq;
                             int64_t pix;
                             over_entry(q, ri, dq, pix);
-                            part += delta_ell_notab(ring.ma[ri] + ring.A[ri].x, dq, load_pc(f.pc, pix), nterms);
+                            const DirectValue dv = notab_value(ring.ma[ri] + ring.A[ri].x, dq, load_pc(f.pc, pix));
+                            part += dv.v;
+                            nterms += dv.terms;
                             ++ndirect;
                         }
                     }
@@ -1695,8 +1699,11 @@ __device__ void wave_series_block(const Frame& f, const State& S, int burn_in, i
     count_work5(S.counters, nterms, nevals, ndirect, nanch, aterms);
 }
 
+// (waves per SIMD: what the registers of the instantiations leave; four entries sit at the edge of three)
+constexpr int wave_occupancy(int nq) { return nq <= 4 ? 3 : nq <= 7 ? 2 : 1; }
+
 template <int NQ>
-__global__ void __launch_bounds__(64) k_wave_series(Frame f, State S, int burn_in, int B, int py, int px, int k0,
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(wave_occupancy(NQ)))) k_wave_series(Frame f, State S, int burn_in, int B, int py, int px, int k0,
                                                     int k1, float* dbg_delta, uint8_t* dbg_acc, int nblk) {
     extern __shared__ double lds_d[];
     int bi, chain;
@@ -3002,7 +3009,7 @@ k_batch(const TileDesc* tiles, const Item* items, const double* inv_tab) {
 
 // Nine-phase block-series items: one wavefront each.
 template <int NQ>
-__global__ void __launch_bounds__(64) k_batch_wave(const TileDesc* tiles, const Item* items) {
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(wave_occupancy(NQ)))) k_batch_wave(const TileDesc* tiles, const Item* items) {
     extern __shared__ double lds_b[];
     const Item I = items[blockIdx.x];
     const TileDesc& T = tiles[I.tile];
